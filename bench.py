@@ -455,10 +455,10 @@ def fwd_kernel_name(res) -> str:
 
 
 def bwd_kernel_names(res) -> list:
-    """The two backward kernels the library dispatches for a workload's shapes (bf16 gradients)."""
+    """The two backward kernels the library dispatches for a workload's shapes (bf16 gradients; grids
+    of more than 1024 blocks of 32 keys, as every workload's here)."""
     d, bm, bn = res["head_dim"], res["block_m"], res["block_n"]
-    dkdv = ("attn_bwd_dkdv_split_kernel<true>" if d == 128 and bn == 128
-            else "attn_bwd_dkdv_kernel<%d, %d, true, false>" % (d, bn // 32))
+    dkdv = "attn_bwd_dkdv_kernel<%d, %d, true, false>" % (d, 4 if d == 128 and bn == 128 else 2)
     return [dkdv, "attn_bwd_dq_kernel<%d, %d, %d, true, false>" % (d, bn, bm // 32)]
 
 

@@ -10,16 +10,14 @@
 // (chunk, k-tile) with the q-tiles listed against it; the workgroup keeps the
 // k-tile's K and V rows (as MFMA B operands) and its dK, dV accumulators in
 // registers for the whole run, looping over the query heads of its K/V head
-// group and over the listed q-tiles in sub-tiles of 64 rows.  Per sub-tile:
+// group and over the listed q-tiles in sub-tiles of 64 or 32 rows.  Per sub-tile:
 //   S  = Q K^T, dP = dO V^T           (lane = key, registers = queries)
 //   P  = exp2(S * scale*log2e - LSE*log2e) on allowed pairs, dS = P (dP - delta)
 //   dV += P^T dO, dK += dS^T Q        (A operands from registers; dO and Q
 //                                      read transposed from LDS)
-// For head_dim 128 with 128-key tiles (every benchmark workload) the split
-// kernel gives each 32-key block to two waves on one SIMD, one forming S, P
-// and dV, the other dP, dS and dK (P handed over through LDS); otherwise one
-// wave owns 32 keys and does all four products.  Q and dO sub-tiles sit in
-// XOR-swizzled LDS tiles (mfma.h).  Each (chunk, k-tile, K/V head) block of
+// Each 32-key block belongs to two waves on one SIMD, one forming S, P and dV,
+// the other dP, dS and dK (P handed over through LDS).  Q and dO sub-tiles sit
+// in XOR-swizzled LDS tiles (mfma.h).  Each (chunk, key block, K/V head) of
 // dK/dV has one owner.
 //
 // dQ kernel: one workgroup per (q-major run, query head), shaped like the
@@ -58,6 +56,9 @@ struct BwdArgs {
   int32_t hkv;
   int32_t group;
   int32_t bm;
+  int32_t bn;
+  int32_t parts;         // dK/dV: workgroups per k-tile (BN / keys of a workgroup)
+  int32_t wide_kv;       // dK/dV: both outputs 16-byte aligned (16-byte accesses)
   float scale;
   float scale_log2;
   int32_t num_tiles;     // tile-list mode: entries of tiles (one chunk's, sorted by q_tile)
@@ -67,41 +68,108 @@ struct BwdArgs {
 // Tile-list mode of the dK/dV kernel: at most this many q-tiles (n / BM) per k-tile.
 constexpr int kMaxListQTiles = 2048;
 
-template <int D, int WAVES, bool BF16OUT, bool LIST = false>
-__global__ __launch_bounds__(64 * WAVES, 1) void attn_bwd_dkdv_kernel(BwdArgs a) {
+// ---------------------------------------------------------------------------
+// dK/dV kernel with split roles: eight waves in four pairs, each pair on one SIMD
+// (wave w and wave w + 4 share one: waves are placed round-robin).  A pair owns
+// 32 keys of the k-tile: its S wave holds the block's K rows as MFMA B operands
+// and its dV accumulators, its dP wave the V rows and the dK accumulators.  Per
+// sub-tile of SUB query rows:
+//   scores    S wave:  S = Q K^T, P = exp2(S * scale*log2e - LSE*log2e) on
+//                      allowed pairs; P (fp16) to LDS for its partner
+//             dP wave: dP = dO V^T
+//   products  S wave:  dV += P^T dO             (dO read transposed)
+//             dP wave: P from LDS, dS = P (dP - delta), dK += dS^T Q
+//                      (Q read transposed)
+// software-pipelined by one sub-tile: iteration t runs the products of t and
+// the scores of t + 1 while later Q and dO rows go from global memory straight
+// into LDS (global_load_lds).  One wave's exponentials (or dS arithmetic) run
+// while the other wave's products occupy the matrix core; S and dP are formed
+// once.
+//
+// The workgroup covers KB key blocks (32 KB keys) with QS = 4 / KB streams of
+// sub-tiles: pair p works on key block p % KB and takes every QS-th sub-tile of
+// the run; the streams' gradients are summed in LDS at the end, in stream
+// order.  KB = 4: one 128-key tile, 64-row sub-tiles, each staged row feeding
+// four key blocks.  KB = 2: 64 keys.  KB = 1: 32 keys; four times the
+// workgroups of KB = 4 with chains a quarter as long, for grids too small to
+// fill the chip, at four times the staging traffic.
+//
+// The two roles are two loops of their own.  Bound by the matrix cores and the LDS
+// reads of the operands, of which neither is saturated (latency of each wave's chain
+// LDS read -> MFMA -> exponentials).  Measured: head_dim 128, 4096 rows of one document
+// x 32 heads 305 -> 290 us (against one loop with a role test per product);
+// head_dim 64, 8192 rows x 32 heads over 8: 602 -> 429 us (against one wave per 32
+// keys doing all four products); tile-list call, 4096 rows x 12 heads over 4:
+// 498 -> 155 us (four streams of 32 keys).
+//
+// LDS ring: three sub-tiles (t: products, t + 1: scores, t + 2: in flight) and
+// one barrier per iteration; KB = 1 at head_dim 128 has room for two only
+// (sub-tile t + 1 is moved during the products of t, with a barrier between
+// the products and the scores).
+// ---------------------------------------------------------------------------
+template <int D, int KB, bool BF16OUT, bool LIST>
+__global__ __launch_bounds__(512, D == 64 && KB == 2 ? 4 : 2) void attn_bwd_dkdv_kernel(BwdArgs a) {
   static_assert(!LIST || !BF16OUT, "the tile-list mode accumulates fp32");
-  constexpr int BN = 32 * WAVES;
-  constexpr int NT = 64 * WAVES;
-  constexpr int SUB = 64;                 // query rows per sub-tile
-  constexpr int CPR = D / 8;              // 16-byte chunks per Q / dO / K row
-  constexpr int MB = D / 32;              // 32-wide blocks of d
-  constexpr int PER_T = SUB * CPR / NT;   // chunks of Q (and of dO) per thread per sub-tile
-  static_assert((SUB * CPR) % NT == 0 && (BN * CPR) % NT == 0, "tiles must split evenly over the threads");
-  static_assert(D == 128 || D == 64, "head_dim 64 or 128");
+  static_assert((D == 128 || D == 64) && (KB == 4 || KB == 2 || KB == 1), "shapes with a kernel");
+  constexpr int QS = 4 / KB;                    // sub-tile streams
+  constexpr int SUB = KB == 4 ? 64 : 32;        // query rows per sub-tile
+  constexpr int QB = SUB / 32;
+  constexpr int RING = D == 128 && KB == 1 ? 2 : 3;
+  constexpr int CPR = D / 8;
+  constexpr int MB = D / 32;
+  constexpr int WCH = SUB * CPR / (2 * KB);     // 16-byte chunks of a Q (or dO) sub-tile a wave moves
+  constexpr int U = WCH / 64;                   // transfer instructions per wave per sub-tile and tensor
+  static_assert(WCH % 64 == 0, "a wave moves whole instructions of a sub-tile");
   constexpr float LOG2E = 1.44269504088896340736f;
-  __shared__ __attribute__((aligned(16))) __bf16 Qs[2][SUB * D];
-  __shared__ __attribute__((aligned(16))) __bf16 dOs[2][SUB * D];
-  __shared__ __attribute__((aligned(16))) float lse_s[2][SUB];
-  __shared__ __attribute__((aligned(16))) float delta_s[2][SUB];
-  __shared__ __attribute__((aligned(16))) int32_t start_s[2][SUB];
-  __shared__ uint32_t qlist[LIST ? kMaxListQTiles : 1];  // tile-list mode: this k-tile's q-tiles (q_tile | kind << 31)
-  __shared__ int32_t wave_hits[WAVES];
+  // LDS: the ring of Q and dO sub-tiles per stream and the P hand-off, used again for the
+  // accumulators at the end (rows padded by 8 floats: the two lane halves of a store, four rows
+  // apart, hit different banks)
+  constexpr int TILE = SUB * D;                                  // elements of one sub-tile
+  constexpr int RING_BYTES = QS * RING * 2 * TILE * 2;
+  // P in fp16 (two buffers with the three-slot ring: P of t + 1 is written while the dP wave reads
+  // P of t), per pair and 32-query block: lane l's 16 values as two 16-byte pieces at [half][l]
+  // (consecutive lanes at consecutive 16 bytes: no bank conflict)
+  constexpr int PBUF = RING - 1;
+  constexpr int P_BYTES = PBUF * 4 * QB * 2 * 64 * 16;
+  constexpr int ACC_STRIDE = D + 8;
+  constexpr int ACC_BYTES = 8 * 32 * ACC_STRIDE * 4;
+  // (tile-list mode: and this k-tile's q-tiles, q_tile | kind << 31, behind the hand-off)
+  constexpr int LOOP_BYTES = RING_BYTES + P_BYTES + (LIST ? 4 * kMaxListQTiles : 0);
+  constexpr int LDS_BYTES = LOOP_BYTES > ACC_BYTES ? LOOP_BYTES : ACC_BYTES;
+  __shared__ __attribute__((aligned(16))) unsigned char raw[LDS_BYTES];
+  __shared__ __attribute__((aligned(16))) float lse_s[QS][RING][SUB];
+  __shared__ __attribute__((aligned(16))) float ndelta_s[QS][RING][SUB];  // -delta
+  __shared__ __attribute__((aligned(16))) int32_t start_s[QS][RING][SUB];
+  __shared__ int32_t wave_hits[LIST ? 8 : 1];
+  uint32_t* const qlist = (uint32_t*)(raw + RING_BYTES + P_BYTES);
+  typedef __attribute__((address_space(3))) void* lds_void;
 
   const int tid = threadIdx.x;
-  const int w = tid >> 6, lane = tid & 63, l32 = lane & 31, hi = lane >> 5;
-  const int run_idx = blockIdx.x / a.hkv;
-  const int g = blockIdx.x - run_idx * a.hkv;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int lane = tid & 63, l32 = lane & 31, hi = lane >> 5;
+  const bool s_wave = w < 4;                // role of the wave
+  const int pair = w & 3;
+  const int kb = pair % KB, qs = pair / KB; // key block, stream
+  __bf16* const ring = (__bf16*)raw + qs * RING * 2 * TILE;  // this stream's [RING][Q | dO]
+  h16x8* const px = (h16x8*)(raw + RING_BYTES) + pair * QB * 2 * 64;  // + pbuf * 4 QB 2 64
+  auto q_tile = [&](int b) { return ring + b * 2 * TILE; };
+  auto o_tile = [&](int b) { return ring + b * 2 * TILE + TILE; };
+
+  // workgroup -> (run, 32 KB-key part of its k-tile, K/V head), heads fastest
+  const int rest = blockIdx.x / a.hkv;
+  const int g = blockIdx.x - rest * a.hkv;
+  const int run_idx = rest / a.parts;
+  const int part = rest - run_idx * a.parts;
   // Run mode: a k-major run from hsap_plan_runs (never empty).  Tile-list mode: k-tile run_idx of
   // chunk a.chunk; the workgroup gathers the tiles with that k_tile from the list (sorted by
   // q_tile) into LDS, in list order, 64 per wave per pass.
-  constexpr bool list_mode = LIST;
-  const hsap_run run = list_mode ? hsap_run{a.chunk, run_idx, 0, 0} : a.runs[run_idx];
-  const int c = list_mode ? a.chunk : a.tiles[run.first].chunk;
+  const hsap_run run = LIST ? hsap_run{a.chunk, run_idx, 0, 0} : a.runs[run_idx];
+  const int c = LIST ? a.chunk : a.tiles[run.first].chunk;
   int count = run.count;
-  if (list_mode) {
-    int total = 0;
-    for (int base = 0; base < a.num_tiles; base += 64 * WAVES) {
-      const int i = base + 64 * w + lane;
+  if constexpr (LIST) {
+    int found = 0;
+    for (int base = 0; base < a.num_tiles; base += 512) {
+      const int i = base + tid;
       bool hit = false;
       uint32_t packed = 0u;
       if (i < a.num_tiles) {
@@ -113,21 +181,21 @@ __global__ __launch_bounds__(64 * WAVES, 1) void attn_bwd_dkdv_kernel(BwdArgs a)
       const int rank = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
       if (lane == 0) wave_hits[w] = __popcll(m);
       __syncthreads();
-      int off = total, all = 0;
-      for (int x = 0; x < WAVES; ++x) {
+      int off = found, all = 0;
+      for (int x = 0; x < 8; ++x) {
         off += x < w ? wave_hits[x] : 0;
         all += wave_hits[x];
       }
       if (hit && off + rank < kMaxListQTiles) qlist[off + rank] = packed;
-      total += all;
+      found += all;
       __syncthreads();  // wave_hits is rewritten by the next pass; qlist is complete after the last
     }
-    count = min(total, kMaxListQTiles);
+    count = __builtin_amdgcn_readfirstlane(min(found, kMaxListQTiles));
     if (count == 0) return;  // no query of the shard reaches this k-tile in the chunk: nothing to add
   }
   const int64_t n = a.geom.n;
-  const int64_t krow0 = (int64_t)run.tile * BN;
-  const int32_t gk = (int32_t)global_pos(a.geom, c, krow0 + 32 * w + l32);  // this lane's key position
+  const int64_t krow0 = (int64_t)run.tile * a.bn + part * (32 * KB);
+  const int32_t gk = (int32_t)global_pos(a.geom, c, krow0 + 32 * kb + l32);  // this lane's key position
   const int64_t kvrow = (int64_t)c * n + krow0;                            // first row in the sharded K/V buffers
 
   // ---- LDS offsets (elements) as lane constants + compile-time immediates -------------
@@ -145,42 +213,24 @@ __global__ __launch_bounds__(64 * WAVES, 1) void attn_bwd_dkdv_kernel(BwdArgs a)
 #pragma unroll
     for (int k = 0; k < 2; ++k) troff[mb][k] = swz<CPR>(8 * k + tr_row, 32 * mb + tr_col) - 8 * k * D;
 
-  // K and V rows of this lane's key as MFMA B operands
-  bf16x8 kf[D / 16], vf[D / 16];
-  {
-    const int64_t off = ((kvrow + 32 * w + l32) * a.hkv + g) * D + 8 * hi;
-#pragma unroll
-    for (int kk = 0; kk < D / 16; ++kk) {
-      kf[kk] = *(const bf16x8*)(a.k + off + 16 * kk);
-      vf[kk] = *(const bf16x8*)(a.v + off + 16 * kk);
-    }
-  }
-
-  f32x16 dk[MB], dv[MB];
-#pragma unroll
-  for (int mb = 0; mb < MB; ++mb) {
-    dk[mb] = f32x16{};
-    dv[mb] = f32x16{};
-  }
-
   const int nsub = a.bm / SUB;
-  const int per_head = count * nsub;
-  const int total = a.group * per_head;
+  const int subs = a.group * count * nsub;        // sub-tiles of the run, over the query heads
+  const int total = (subs + QS - 1) / QS;         // iterations: sub-tiles QS t + qs
+  uint32_t win0 = 0u, win1 = 0u;
+  int win_lo = 0, win_hi = -1;
   // The run's q-tiles, packed one per lane (q_tile | kind << 31) in windows of 64 tiles, read
   // with v_readlane: the next sub-tile's address never waits on a memory load.  Window v lives
   // in win0 (v even) or win1 (v odd); sub-tiles visit the run's tiles in order once per query
   // head, so the window is reloaded when the tile index leaves it.
-  uint32_t win0 = 0u, win1 = 0u;
-  int win_lo = 0, win_hi = -1;  // windows held: win_lo (and win_lo + 1 when win_hi > win_lo)
   auto load_window = [&](int v) {
     const int i = 64 * v + lane;
     uint32_t p = 0;
     if (i < count) {
-      if (!list_mode) {
+      if constexpr (LIST) {
+        p = qlist[i];
+      } else {
         const hsap_tile t = a.tiles[run.first + i];
         p = (uint32_t)t.q_tile | ((uint32_t)t.kind << 31);
-      } else {
-        p = qlist[i];
       }
     }
     if (v & 1) win1 = p;
@@ -193,274 +243,27 @@ __global__ __launch_bounds__(64 * WAVES, 1) void attn_bwd_dkdv_kernel(BwdArgs a)
     else win_lo = v;
     win_hi = v;
   };
-  // sub-tile `it`: query head, tile of the run (packed), 64-row slice of the tile
-  auto head_of = [&](int it) { return g * a.group + it / per_head; };
-  auto tile_of = [&](int it) -> uint32_t {
-    const int idx = (it % per_head) / nsub;
-    return __builtin_amdgcn_readlane(((idx >> 6) & 1) ? win1 : win0, idx & 63);
-  };
-  auto q0_of = [&](uint32_t t, int it) {
-    return (int64_t)(t & 0x7FFFFFFFu) * a.bm + ((it % per_head) % nsub) * SUB;
-  };
-  ensure_window(0);
-
-  // staging of one sub-tile: Q and dO rows, and the per-row LSE, delta and document start
-  int32_t soff[PER_T], loff[PER_T];
-#pragma unroll
-  for (int i = 0; i < PER_T; ++i) {
-    const int idx = tid + i * NT, row = idx / CPR, cc = idx % CPR;
-    soff[i] = row * a.hq * D + cc * 8;
-    loff[i] = swz<CPR>(row, cc * 8);
-  }
-  bf16x8 qreg[PER_T], oreg[PER_T];
-  float lreg = 0.f, dreg = 0.f;
-  int32_t sreg = 0;
-  auto load_sub = [&](int it) {
-    const int h = head_of(it);
-    ensure_window(((it % per_head) / nsub) >> 6);
-    const uint32_t t = tile_of(it);
-    const int64_t q0 = q0_of(t, it);
-    const int64_t base = (q0 * a.hq + h) * D;
-#pragma unroll
-    for (int i = 0; i < PER_T; ++i) {
-      qreg[i] = *(const bf16x8*)(a.q + base + soff[i]);
-      oreg[i] = *(const bf16x8*)(a.d_o + base + soff[i]);
-    }
-    if (tid < SUB) {
-      lreg = a.lse[(int64_t)h * n + q0 + tid];
-      dreg = a.delta[(int64_t)h * n + q0 + tid];
-      sreg = a.doc_start[global_pos(a.geom, a.shard, q0) + tid];
-    }
-  };
-  auto store_sub = [&](int buf) {
-#pragma unroll
-    for (int i = 0; i < PER_T; ++i) {
-      *(bf16x8*)(&Qs[buf][loff[i]]) = qreg[i];
-      *(bf16x8*)(&dOs[buf][loff[i]]) = oreg[i];
-    }
-    if (tid < SUB) {
-      lse_s[buf][tid] = lreg == -__builtin_inff() ? __builtin_inff() : lreg * LOG2E;  // no key: P = 0
-      delta_s[buf][tid] = dreg;
-      start_s[buf][tid] = sreg;
-    }
-  };
-
-  load_sub(0);
-  store_sub(0);
-  __syncthreads();
-
-  for (int it = 0; it < total; ++it) {
-    const int buf = it & 1;
-    const int h = head_of(it);
-    const uint32_t tile = tile_of(it);
-    const int64_t q0 = q0_of(tile, it);
-    const int32_t gq0 = (int32_t)global_pos(a.geom, a.shard, q0);
-    const bool masked = (tile >> 31) != 0;
-    if (it + 1 < total) load_sub(it + 1);
-    const __bf16* Q = Qs[buf];
-    const __bf16* O = dOs[buf];
-
-    // per block of 32 queries: S = Q K^T, dP = dO V^T (register j = query 32 qb + c_row(j, hi)),
-    // then P and dS, then dV += P^T dO and dK += dS^T Q, then dS^T to LDS
-#pragma unroll
-    for (int qb = 0; qb < SUB / 32; ++qb) {
-      f32x16 sacc{}, dpacc{};
-      bf16x8 qa[D / 16], oa[D / 16];  // all operand reads of the block first, then the MFMAs
-#pragma unroll
-      for (int kk = 0; kk < D / 16; ++kk) {
-        qa[kk] = *(const bf16x8*)(Q + 32 * qb * D + rowoff[kk]);
-        oa[kk] = *(const bf16x8*)(O + 32 * qb * D + rowoff[kk]);
-      }
-#pragma unroll
-      for (int kk = 0; kk < D / 16; ++kk) {
-        sacc = mfma32(qa[kk], kf[kk], sacc);
-        dpacc = mfma32(oa[kk], vf[kk], dpacc);
-      }
-      // the transposed dO and Q reads of the dV / dK products depend on no score: issued here, they
-      // land while P and dS are computed (one wave per SIMD has nothing else to hide them)
-      bf16x8 bo[2][MB], bq[2][MB];
-#pragma unroll
-      for (int half = 0; half < 2; ++half) {
-        const int rb = (32 * qb + 16 * half) * D;
-#pragma unroll
-        for (int mb = 0; mb < MB; ++mb) {
-          bo[half][mb] = cat4(ds_read_tr16(O + rb + troff[mb][0]), ds_read_tr16(O + rb + 8 * D + troff[mb][1]));
-          bq[half][mb] = cat4(ds_read_tr16(Q + rb + troff[mb][0]), ds_read_tr16(Q + rb + 8 * D + troff[mb][1]));
-        }
-      }
-      // P for the block (register j = 4 grp + e holds query q4 + e, q4 = 32 qb + 8 grp + 4 hi),
-      // masked in one uniform branch, then P and dS = P (dP - delta) as bf16
-      float p[16];
-#pragma unroll
-      for (int grp = 0; grp < 4; ++grp) {
-        const f32x4 l4 = *(const f32x4*)(&lse_s[buf][32 * qb + 8 * grp + 4 * hi]);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) p[4 * grp + e] = fast_exp2(__builtin_fmaf(sacc[4 * grp + e], a.scale_log2, -l4[e]));
-      }
-      if (masked) {
-#pragma unroll
-        for (int grp = 0; grp < 4; ++grp) {
-          const int q4 = 32 * qb + 8 * grp + 4 * hi;
-          const i32x4 s4 = *(const i32x4*)(&start_s[buf][q4]);
-#pragma unroll
-          for (int e = 0; e < 4; ++e)
-            if ((uint32_t)(gk - s4[e]) > (uint32_t)(gq0 + q4 + e - s4[e])) p[4 * grp + e] = 0.f;
-        }
-      }
-      bf16x8 pb[2], sb[2];
-#pragma unroll
-      for (int grp = 0; grp < 4; ++grp) {
-        const f32x4 d4 = *(const f32x4*)(&delta_s[buf][32 * qb + 8 * grp + 4 * hi]);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const int j = 4 * grp + e;
-          pb[j >> 3][j & 7] = (__bf16)p[j];
-          sb[j >> 3][j & 7] = (__bf16)(p[j] * (dpacc[j] - d4[e]));
-        }
-      }
-#pragma unroll
-      for (int half = 0; half < 2; ++half)
-#pragma unroll
-        for (int mb = 0; mb < MB; ++mb) {
-          dv[mb] = mfma32(pb[half], bo[half][mb], dv[mb]);
-          dk[mb] = mfma32(sb[half], bq[half][mb], dk[mb]);
-        }
-    }
-
-    if (it + 1 < total) store_sub(buf ^ 1);
-    hsap_lds_barrier();
-  }
-
-  // this workgroup owns rows [krow0, krow0 + BN) of chunk c for K/V head g: plain read-add-write
-  // of the fp32 accumulators, or a store of the final bf16 values
-#pragma unroll
-  for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-    for (int j = 0; j < 16; ++j) {
-      const int64_t idx = ((kvrow + 32 * w + c_row(j, hi)) * a.hkv + g) * D + 32 * mb + l32;
-      if (BF16OUT) {
-        a.dk16[idx] = (__bf16)(dk[mb][j] * a.scale);
-        a.dv16[idx] = (__bf16)dv[mb][j];
-      } else {
-        a.dk[idx] += dk[mb][j] * a.scale;
-        a.dv[idx] += dv[mb][j];
-      }
-    }
-}
-
-// ---------------------------------------------------------------------------
-// dK/dV kernel with split roles (head_dim 128, BN = 128): eight waves, two per
-// key block of 32 keys.  Wave kb (0..3) is the block's S wave: it holds the
-// block's K rows as MFMA B operands and its dV accumulators; wave 4 + kb is
-// the dP wave: V rows and dK accumulators.  Per 64-row q sub-tile:
-//   scores    S wave:  S = Q K^T, P = exp2(S * scale*log2e - LSE*log2e) on
-//                      allowed pairs; P (fp16) to LDS for its partner
-//             dP wave: dP = dO V^T
-//   products  S wave:  dV += P^T dO             (dO read transposed)
-//             dP wave: P from LDS, dS = P (dP - delta), dK += dS^T Q
-//                      (Q read transposed)
-// software-pipelined by one sub-tile: iteration t runs the products of t and
-// the scores of t + 1, with one barrier, while the Q and dO rows of t + 2 go
-// from global memory straight into LDS (global_load_lds).
-// Each wave issues 32 MFMAs per sub-tile, half of the one-wave-per-block
-// kernel's 64, and holds half its state (K or V, dK or dV), so two waves fit
-// on a SIMD: one wave's exponentials (or dS arithmetic) run while the other
-// wave's products occupy the matrix core.  S and dP are formed once.
-// Wave w and wave w + 4 share a SIMD (waves are placed round-robin).
-// ---------------------------------------------------------------------------
-template <bool BF16OUT>
-__global__ __launch_bounds__(512, 2) void attn_bwd_dkdv_split_kernel(BwdArgs a) {
-  constexpr int D = 128, WAVES = 8, KB = 4;  // KB key blocks of 32: BN = 128
-  constexpr int NT = 64 * WAVES;
-  constexpr int SUB = 64;
-  constexpr int CPR = D / 8;
-  constexpr int MB = D / 32;
-  constexpr int WCH = SUB * CPR / WAVES;       // 16-byte chunks of a Q (or dO) sub-tile a wave moves
-  constexpr int U = WCH / 64;                   // transfer instructions per wave per sub-tile and tensor
-  static_assert(WCH % 64 == 0, "a wave moves whole instructions of a sub-tile");
-  constexpr float LOG2E = 1.44269504088896340736f;
-  // a ring of three sub-tiles: t (gradient products), t + 1 (scores), t + 2 (in flight)
-  __shared__ __attribute__((aligned(16))) __bf16 Qs[3][SUB * D];
-  __shared__ __attribute__((aligned(16))) __bf16 dOs[3][SUB * D];
-  __shared__ __attribute__((aligned(16))) float lse_s[3][SUB];
-  __shared__ __attribute__((aligned(16))) float ndelta_s[3][SUB];  // -delta
-  __shared__ __attribute__((aligned(16))) int32_t start_s[3][SUB];
-  // P hand-off in fp16 (two buffers: P of sub-tile t + 1 is written while the dP wave reads P of
-  // t), per key block and 32-query block: lane l's 16 values as two 16-byte pieces at [half][l]
-  // (consecutive lanes at consecutive 16 bytes: no bank conflict)
-  __shared__ __attribute__((aligned(16))) h16x8 Px[2][KB][SUB / 32][2][64];
-  typedef __attribute__((address_space(3))) void* lds_void;
-
-  const int tid = threadIdx.x;
-  const int w = tid >> 6, lane = tid & 63, l32 = lane & 31, hi = lane >> 5;
-  const bool s_wave = w < KB;               // wave-uniform role
-  const int kb = s_wave ? w : w - KB;       // key block
-  const int run_idx = blockIdx.x / a.hkv;
-  const int g = blockIdx.x - run_idx * a.hkv;
-  const hsap_run run = a.runs[run_idx];
-  const int c = a.tiles[run.first].chunk;  // k-major runs are never empty
-  const int count = run.count;
-  const int64_t n = a.geom.n;
-  const int64_t krow0 = (int64_t)run.tile * (32 * KB);
-  const int32_t gk = (int32_t)global_pos(a.geom, c, krow0 + 32 * kb + l32);  // this lane's key position
-  const int64_t kvrow = (int64_t)c * n + krow0;
-
-  // row reads (row 32 qb + l32, chunk 2 kk + hi) and transpose reads of the swizzled tiles, as in
-  // the one-wave-per-block kernel
-  const int tr_row = 4 * hi + ((lane & 15) >> 2);
-  const int tr_col = 16 * ((lane >> 4) & 1) + 4 * (lane & 3);
-  int rowoff[D / 16], troff[MB][2];
-#pragma unroll
-  for (int kk = 0; kk < D / 16; ++kk) rowoff[kk] = swz<CPR>(l32, 16 * kk + 8 * hi);
-#pragma unroll
-  for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-    for (int k = 0; k < 2; ++k) troff[mb][k] = swz<CPR>(8 * k + tr_row, 32 * mb + tr_col) - 8 * k * D;
-
-  // this lane's key row of K (S wave) or V (dP wave) as MFMA B operands
-  bf16x8 kv[D / 16];
-  {
-    const __bf16* src = s_wave ? a.k : a.v;
-    const int64_t off = ((kvrow + 32 * kb + l32) * a.hkv + g) * D + 8 * hi;
-#pragma unroll
-    for (int kk = 0; kk < D / 16; ++kk) kv[kk] = *(const bf16x8*)(src + off + 16 * kk);
-  }
-  f32x16 acc[MB];  // dV (S wave) or dK (dP wave)
-#pragma unroll
-  for (int mb = 0; mb < MB; ++mb) acc[mb] = f32x16{};
-
-  const int nsub = a.bm / SUB;
-  const int total = a.group * count * nsub;
-  uint32_t win0 = 0u, win1 = 0u;
-  int win_lo = 0, win_hi = -1;
-  auto load_window = [&](int v) {
-    const int i = 64 * v + lane;
-    uint32_t p = 0;
-    if (i < count) {
-      const hsap_tile t = a.tiles[run.first + i];
-      p = (uint32_t)t.q_tile | ((uint32_t)t.kind << 31);
-    }
-    if (v & 1) win1 = p;
-    else win0 = p;
-  };
-  auto ensure_window = [&](int v) {
-    if (v >= win_lo && v <= win_hi) return;
-    load_window(v);
-    if (v == win_hi + 1 && v - 1 >= win_lo) win_lo = v - 1;
-    else win_lo = v;
-    win_hi = v;
-  };
   // Sub-tile position as counters (no division in the loop): query head h, tile index idx in the
-  // run, 64-row slice sb of the tile; the next sub-tile's counters advance one step at a time.
+  // run, SUB-row slice sb of the tile; left = sub-tiles behind this one.  A stream that has run out
+  // (its last iteration may lie past the end) repeats the run's last sub-tile with P = 0.
   struct Pos {
-    int h, idx, sb;
+    int h, idx, sb, left;
+    bool past;
   };
   auto advance = [&](Pos p) {
-    if (++p.sb == nsub) {
-      p.sb = 0;
-      if (++p.idx == count) {
-        p.idx = 0;
-        ++p.h;
+#pragma unroll
+    for (int i = 0; i < QS; ++i) {
+      if (QS > 1 && p.left == 0) {
+        p.past = true;
+        break;
+      }
+      --p.left;
+      if (++p.sb == nsub) {
+        p.sb = 0;
+        if (++p.idx == count) {
+          p.idx = 0;
+          ++p.h;
+        }
       }
     }
     return p;
@@ -469,210 +272,312 @@ __global__ __launch_bounds__(512, 2) void attn_bwd_dkdv_split_kernel(BwdArgs a) 
     return __builtin_amdgcn_readlane(((p.idx >> 6) & 1) ? win1 : win0, p.idx & 63);
   };
   auto q0_at = [&](uint32_t t, const Pos& p) { return (int64_t)(t & 0x7FFFFFFFu) * a.bm + p.sb * SUB; };
-  ensure_window(0);
 
-  // Q and dO sub-tiles by direct-to-LDS transfers: instruction u of wave w fills chunk positions
-  // p = WCH w + 64 u + lane of the swizzled tile; the lane's source is the chunk the swizzle places
-  // there, a 32-bit byte offset from the sub-tile's scalar base (Q and dO rows have the same stride)
+  // Q and dO sub-tiles by direct-to-LDS transfers: instruction u of the stream's wave x fills chunk
+  // positions p = WCH x + 64 u + lane of the swizzled tile; the lane's source is the chunk the
+  // swizzle places there, a 32-bit byte offset from the sub-tile's scalar base (Q and dO rows have
+  // the same stride)
+  const int x = kb + (s_wave ? 0 : KB);
   uint32_t gsrc[U];
 #pragma unroll
   for (int u = 0; u < U; ++u) {
-    const int p = WCH * w + 64 * u + lane, row = p / CPR;
+    const int p = WCH * x + 64 * u + lane, row = p / CPR;
     gsrc[u] = (uint32_t)((row * a.hq * D + swz_chunk<CPR>(row, p % CPR) * 8) * 2);
   }
-  const int wu = __builtin_amdgcn_readfirstlane(w);
   auto stage = [&](const __bf16* src, __bf16* dst) {
-    const uint32_t lds = (uint32_t)(uintptr_t)(lds_void)dst + (uint32_t)(WCH * wu * 16);
+    const uint32_t lds = (uint32_t)(uintptr_t)(lds_void)dst + (uint32_t)(WCH * x * 16);
 #pragma unroll
     for (int u = 0; u < U; ++u)
       asm volatile("global_load_lds_dwordx4 %0, %1" ::"v"(gsrc[u]), "s"(src), "{m0}"(lds + 64 * 16 * u));
   };
-  float lreg = 0.f, dreg = 0.f;
-  int32_t sreg = 0;
-  // the sub-tile's Q and dO into buffer buf (transfers), its LSE, delta and document starts into
-  // registers of the first 64 threads (written to LDS by store_sub)
-  auto load_sub = [&](const Pos& ps, int buf) {
-    const int h = g * a.group + ps.h;
-    ensure_window(ps.idx >> 6);
-    const uint32_t t = tile_at(ps);
-    const int64_t q0 = q0_at(t, ps);
-    const int64_t base = (q0 * a.hq + h) * D;
-    stage(a.q + base, Qs[buf]);
-    stage(a.d_o + base, dOs[buf]);
-    if (tid < SUB) {
-      lreg = a.lse[(int64_t)h * n + q0 + tid];
-      dreg = a.delta[(int64_t)h * n + q0 + tid];
-      sreg = a.doc_start[global_pos(a.geom, a.shard, q0) + tid];
+  // One role's whole run (S: K rows and dV; otherwise V rows and dK).  The two loops are separate
+  // code, so each is one straight-line block per iteration for the compiler to order.
+  auto work = [&](auto role) __attribute__((always_inline)) {
+    constexpr bool S = decltype(role)::value;
+    // this lane's key row of K (S) or V as MFMA B operands
+    bf16x8 kv[D / 16];
+    {
+      const __bf16* src = S ? a.k : a.v;
+      const int64_t off = ((kvrow + 32 * kb + l32) * a.hkv + g) * D + 8 * hi;
+#pragma unroll
+      for (int kk = 0; kk < D / 16; ++kk) kv[kk] = *(const bf16x8*)(src + off + 16 * kk);
     }
-  };
-  auto store_sub = [&](int buf) {
-    if (tid < SUB) {
-      lse_s[buf][tid] = lreg == -__builtin_inff() ? __builtin_inff() : lreg * LOG2E;  // no key: P = 0
-      ndelta_s[buf][tid] = -dreg;
-      start_s[buf][tid] = sreg;
-    }
-  };
+    f32x16 acc[MB];  // dV (S) or dK
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb) acc[mb] = f32x16{};
 
-  // Scores of a sub-tile from its rows (buffer rb): S = Q K^T (S wave) or dP = dO V^T (dP wave)
-  // into sp; the S wave turns them into P (register j = 4 grp + e holds query q4 + e,
-  // q4 = 32 qb + 8 grp + 4 hi; P = exp2(S * scale*log2e - LSE*log2e), masked in one uniform
-  // branch), kept in bf16 as its own next A operand and handed to the dP wave in fp16.
-  f32x16 sp[SUB / 32];
-  bf16x8 opnd[SUB / 32][2];  // A operands of the gradient products: P (S wave) or dS (dP wave)
-  auto scores = [&](int rb, int pbuf, bool masked, int32_t gq0) {
-    const __bf16* R = s_wave ? Qs[rb] : dOs[rb];
+    float lreg = 0.f, dreg = 0.f;
+    int32_t sreg = 0;
+    const bool row_lane = S && kb == 0 && lane < SUB;  // this stream's lanes that bring the per-row values
+    // the sub-tile's Q and dO into buffer buf (transfers), its LSE, delta and document starts into
+    // registers of SUB lanes (written to LDS by store_sub)
+    auto load_sub = [&](const Pos& ps, int buf) {
+      // (uniform across the wave, which the transfers' scalar bases need the compiler to know)
+      const int h = __builtin_amdgcn_readfirstlane(g * a.group + ps.h);
+      ensure_window(ps.idx >> 6);
+      const uint32_t t = tile_at(ps);
+      const int64_t q0 = __builtin_amdgcn_readfirstlane((int)q0_at(t, ps));
+      const int64_t base = (q0 * a.hq + h) * D;
+      stage(a.q + base, q_tile(buf));
+      stage(a.d_o + base, o_tile(buf));
+      if (row_lane) {
+        lreg = ps.past ? -__builtin_inff() : a.lse[(int64_t)h * n + q0 + lane];
+        dreg = a.delta[(int64_t)h * n + q0 + lane];
+        sreg = a.doc_start[global_pos(a.geom, a.shard, q0) + lane];
+      }
+    };
+    auto store_sub = [&](int buf) {
+      if (row_lane) {
+        lse_s[qs][buf][lane] = lreg == -__builtin_inff() ? __builtin_inff() : lreg * LOG2E;  // no key: P = 0
+        ndelta_s[qs][buf][lane] = -dreg;
+        start_s[qs][buf][lane] = sreg;
+      }
+    };
+
+    // Scores of a sub-tile from its rows (buffer rb): S = Q K^T or dP = dO V^T into sp, the latter
+    // accumulated onto -delta of each query (register j = 4 cq + e), so the chain ends with
+    // dP - delta and dS takes one multiply per element.
+    auto scores = [&](int rb, f32x16 (&sp)[QB]) __attribute__((always_inline)) {
+      const __bf16* R = S ? q_tile(rb) : o_tile(rb);
 #pragma unroll
-    for (int qb = 0; qb < SUB / 32; ++qb) {
-      bf16x8 ra[D / 16];
+      for (int qb = 0; qb < QB; ++qb) {
+        bf16x8 ra[D / 16];
 #pragma unroll
-      for (int kk = 0; kk < D / 16; ++kk) ra[kk] = *(const bf16x8*)(R + 32 * qb * D + rowoff[kk]);
-      if (s_wave) {
-        sp[qb] = f32x16{};
+        for (int kk = 0; kk < D / 16; ++kk) ra[kk] = *(const bf16x8*)(R + 32 * qb * D + rowoff[kk]);
+        if constexpr (S) {
+          sp[qb] = f32x16{};
+        } else {
+          f32x16 init;
 #pragma unroll
-        for (int kk = 0; kk < D / 16; ++kk) sp[qb] = mfma32(ra[kk], kv[kk], sp[qb]);
-      } else {
-        // the products accumulate onto -delta of each query (register j = 4 cq + e), so the
-        // chain ends with dP - delta and dS takes one multiply per element
-        f32x16 init;
+          for (int cq = 0; cq < 4; ++cq) {
+            const f32x4 d4 = *(const f32x4*)(&ndelta_s[qs][rb][32 * qb + 8 * cq + 4 * hi]);
 #pragma unroll
-        for (int cq = 0; cq < 4; ++cq) {
-          const f32x4 d4 = *(const f32x4*)(&ndelta_s[rb][32 * qb + 8 * cq + 4 * hi]);
-#pragma unroll
-          for (int e = 0; e < 4; ++e) init[4 * cq + e] = d4[e];
+            for (int e = 0; e < 4; ++e) init[4 * cq + e] = d4[e];
+          }
+          sp[qb] = init;
         }
-        sp[qb] = init;
 #pragma unroll
         for (int kk = 0; kk < D / 16; ++kk) sp[qb] = mfma32(ra[kk], kv[kk], sp[qb]);
       }
-    }
-    if (s_wave) {
+    };
+    // P of a sub-tile (register j = 4 grp + e holds query q4 + e, q4 = 32 qb + 8 grp + 4 hi;
+    // P = exp2(S * scale*log2e - LSE*log2e), masked in one uniform branch): in bf16 as this wave's
+    // next A operand, in fp16 to the dP wave.
+    auto probs = [&](int rb, f32x16 (&sp)[QB]) __attribute__((always_inline)) {
 #pragma unroll
-      for (int qb = 0; qb < SUB / 32; ++qb) {
-        float p[16];
+      for (int qb = 0; qb < QB; ++qb)
 #pragma unroll
         for (int grp = 0; grp < 4; ++grp) {
-          const f32x4 l4 = *(const f32x4*)(&lse_s[rb][32 * qb + 8 * grp + 4 * hi]);
+          const f32x4 l4 = *(const f32x4*)(&lse_s[qs][rb][32 * qb + 8 * grp + 4 * hi]);
 #pragma unroll
-          for (int e = 0; e < 4; ++e) p[4 * grp + e] = fast_exp2(__builtin_fmaf(sp[qb][4 * grp + e], a.scale_log2, -l4[e]));
+          for (int e = 0; e < 4; ++e)
+            sp[qb][4 * grp + e] = fast_exp2(__builtin_fmaf(sp[qb][4 * grp + e], a.scale_log2, -l4[e]));
         }
-        if (masked) {
+    };
+    auto hand_over = [&](int rb, int pbuf, bool masked, int32_t gq0, f32x16 (&sp)[QB], bf16x8 (&opnd)[QB][2])
+                         __attribute__((always_inline)) {
+      if (masked) {
+#pragma unroll
+        for (int qb = 0; qb < QB; ++qb)
 #pragma unroll
           for (int grp = 0; grp < 4; ++grp) {
             const int q4 = 32 * qb + 8 * grp + 4 * hi;
-            const i32x4 s4 = *(const i32x4*)(&start_s[rb][q4]);
+            const i32x4 s4 = *(const i32x4*)(&start_s[qs][rb][q4]);
 #pragma unroll
             for (int e = 0; e < 4; ++e)
-              if ((uint32_t)(gk - s4[e]) > (uint32_t)(gq0 + q4 + e - s4[e])) p[4 * grp + e] = 0.f;
+              if ((uint32_t)(gk - s4[e]) > (uint32_t)(gq0 + q4 + e - s4[e])) sp[qb][4 * grp + e] = 0.f;
           }
-        }
+      }
+#pragma unroll
+      for (int qb = 0; qb < QB; ++qb) {
 #pragma unroll
         for (int half = 0; half < 2; ++half) {
           h16x8 ph;
 #pragma unroll
           for (int i = 0; i < 4; ++i) {
-            const auto pk = __builtin_amdgcn_cvt_pkrtz(p[8 * half + 2 * i], p[8 * half + 2 * i + 1]);
+            const auto pk = __builtin_amdgcn_cvt_pkrtz(sp[qb][8 * half + 2 * i], sp[qb][8 * half + 2 * i + 1]);
             ph[2 * i] = pk[0];
             ph[2 * i + 1] = pk[1];
           }
-          Px[pbuf][kb][qb][half][lane] = ph;
+          px[(pbuf * 4 * QB + qb) * 128 + half * 64 + lane] = ph;
         }
 #pragma unroll
-        for (int j = 0; j < 16; ++j) opnd[qb][j >> 3][j & 7] = (__bf16)p[j];
+        for (int j = 0; j < 16; ++j) opnd[qb][j >> 3][j & 7] = (__bf16)sp[qb][j];
       }
-    }
-  };
-  // Gradient products of a sub-tile (buffer tb): dV += P^T dO (S wave, dO read transposed) or
-  // dS = P (dP - delta), dK += dS^T Q (dP wave, P from the hand-off, Q read transposed)
-  auto products = [&](int tb, int pbuf) {
-    const __bf16* T = s_wave ? dOs[tb] : Qs[tb];
+    };
+    // dS = P (dP - delta) of a sub-tile: one mixed-precision multiply per element (fp16 P)
+    auto take_over = [&](int pbuf, const f32x16 (&sp)[QB], bf16x8 (&opnd)[QB][2]) __attribute__((always_inline)) {
 #pragma unroll
-    for (int qb = 0; qb < SUB / 32; ++qb) {
-      bf16x8 bt[2][MB];  // 16 queries per MFMA
-#pragma unroll
-      for (int half = 0; half < 2; ++half) {
-        const int rb = (32 * qb + 16 * half) * D;
-#pragma unroll
-        for (int mb = 0; mb < MB; ++mb)
-          bt[half][mb] = cat4(ds_read_tr16(T + rb + troff[mb][0]), ds_read_tr16(T + rb + 8 * D + troff[mb][1]));
-      }
-      if (!s_wave) {
-        // dS = P (dP - delta): one mixed-precision multiply per element (fp16 P, fp32 dP - delta)
-        const h16x8 ph[2] = {Px[pbuf][kb][qb][0][lane], Px[pbuf][kb][qb][1][lane]};
+      for (int qb = 0; qb < QB; ++qb) {
+        const h16x8 ph[2] = {px[(pbuf * 4 * QB + qb) * 128 + lane], px[(pbuf * 4 * QB + qb) * 128 + 64 + lane]};
 #pragma unroll
         for (int j = 0; j < 16; ++j)
           opnd[qb][j >> 3][j & 7] = (__bf16)__builtin_fmaf((float)ph[j >> 3][j & 7], sp[qb][j], 0.f);
       }
+    };
+    // Gradient products of a sub-tile (buffer tb): dV += P^T dO or dK += dS^T Q, dO and Q read
+    // transposed, 16 queries per MFMA
+    auto products = [&](int tb, const bf16x8 (&opnd)[QB][2]) __attribute__((always_inline)) {
+      const __bf16* T = S ? o_tile(tb) : q_tile(tb);
 #pragma unroll
-      for (int half = 0; half < 2; ++half)
+      for (int qb = 0; qb < QB; ++qb)
 #pragma unroll
-        for (int mb = 0; mb < MB; ++mb) acc[mb] = mfma32(opnd[qb][half], bt[half][mb], acc[mb]);
+        for (int half = 0; half < 2; ++half) {
+          const int rb = (32 * qb + 16 * half) * D;
+#pragma unroll
+          for (int mb = 0; mb < MB; ++mb) {
+            const bf16x8 bt = cat4(ds_read_tr16(T + rb + troff[mb][0]), ds_read_tr16(T + rb + 8 * D + troff[mb][1]));
+            acc[mb] = mfma32(opnd[qb][half], bt, acc[mb]);
+          }
+        }
+    };
+    auto sub_mask = [&](const Pos& p, bool& masked, int32_t& gq0) {
+      const uint32_t t = tile_at(p);
+      masked = (t >> 31) != 0;
+      gq0 = (int32_t)global_pos(a.geom, a.shard, q0_at(t, p));
+    };
+
+    // prologue: the first sub-tiles staged, the scores of sub-tile 0
+    ensure_window(0);
+    Pos cur{0, 0, 0, subs - 1, false};
+    if constexpr (QS > 1) {  // stream qs starts qs sub-tiles in
+      cur.past = qs >= subs;
+      const int i = min(qs, subs - 1);
+      cur.left = subs - 1 - i;
+      cur.sb = i % nsub;
+      cur.idx = i / nsub % count;
+      cur.h = i / nsub / count;
     }
-  };
-  auto sub_mask = [&](const Pos& p, bool& masked, int32_t& gq0) {
-    const uint32_t t = tile_at(p);
-    masked = (t >> 31) != 0;
-    gq0 = (int32_t)global_pos(a.geom, a.shard, q0_at(t, p));
-  };
-
-  // prologue: sub-tiles 0 and 1 staged, the scores of sub-tile 0
-  Pos cur{0, 0, 0};
-  Pos nx1 = advance(cur);
-  bool m0;
-  int32_t g0;
-  sub_mask(cur, m0, g0);
-  load_sub(cur, 0);
-  store_sub(0);
-  if (total > 1) {
-    load_sub(nx1, 1);
-    store_sub(1);
-  }
-  // The compiler does not see the waits inside asm statements: without a use of the K (or V) rows
-  // here it would wait for their loads at their first use inside the loop, in every iteration,
-  // and since the counter also counts the transfers, each iteration would wait for the next
-  // sub-tiles before its first product.
+    Pos nx1 = advance(cur);
+    bool m0;
+    int32_t g0;
+    sub_mask(cur, m0, g0);
+    load_sub(cur, 0);
+    store_sub(0);
+    if (RING == 3 && total > 1) {
+      load_sub(nx1, 1);
+      store_sub(1);
+    }
+    // The compiler does not see the waits inside asm statements: without a use of the K (or V) rows
+    // here it would wait for their loads at their first use inside the loop, in every iteration,
+    // and since the counter also counts the transfers, each iteration would wait for the next
+    // sub-tiles before its first product.
 #pragma unroll
-  for (int kk = 0; kk < D / 16; ++kk) asm volatile("" ::"v"(kv[kk]));
-  asm volatile("s_waitcnt vmcnt(0)\n\ts_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-  scores(0, 0, m0, g0);
-  hsap_lds_barrier();  // P of sub-tile 0 is in LDS
-
-  // Iteration t: the gradient products of sub-tile t, then the scores of sub-tile t + 1, while
-  // sub-tile t + 2 is moved into the third buffer; one barrier.  Both waves of a SIMD start with
-  // independent work (the S wave's products on P it holds, the dP wave's dS arithmetic) and the S
-  // wave's exponentials follow its score products while the dP wave's products run.
-  int b0 = 0;  // t % 3
-  for (int t = 0; t < total; ++t) {
-    const int b1 = b0 == 2 ? 0 : b0 + 1, b2 = b1 == 2 ? 0 : b1 + 1;
-    const Pos nx2 = advance(nx1);
-    bool m1 = false;
-    int32_t g1 = 0;
-    if (t + 1 < total) sub_mask(nx1, m1, g1);  // before the window of t + 2 may replace it
-    if (t + 2 < total) load_sub(nx2, b2);       // buffer b2 was last read before the previous barrier
-    products(b0, t & 1);
-    if (t + 1 < total) scores(b1, (t + 1) & 1, m1, g1);
-    if (t + 2 < total) store_sub(b2);
-    // sub-tile t + 2 has landed and is staged; P of t + 1 is in LDS; buffer b0 is free
+    for (int kk = 0; kk < D / 16; ++kk) asm volatile("" ::"v"(kv[kk]));
     asm volatile("s_waitcnt vmcnt(0)\n\ts_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-    nx1 = nx2;
-    b0 = b1;
-  }
+    f32x16 sp[QB];
+    bf16x8 opnd[QB][2];  // A operands of the gradient products: P (S) or dS
+    scores(0, sp);
+    if constexpr (S) {
+      probs(0, sp);
+      hand_over(0, 0, m0, g0, sp, opnd);
+    }
+    hsap_lds_barrier();  // P of sub-tile 0 is in LDS
 
-  // this workgroup owns rows [krow0, krow0 + 128) of chunk c for K/V head g: the S waves write dV,
-  // the dP waves dK (scaled)
-  const float mul = s_wave ? 1.f : a.scale;
+    if constexpr (RING == 3) {
+      // Iteration t: the gradient products of sub-tile t and the scores of sub-tile t + 1, while
+      // sub-tile t + 2 is moved into the third buffer; one barrier.
+      int b0 = 0;  // t % 3
+      for (int t = 0; t + 1 < total; ++t) {
+        const int b1 = b0 == 2 ? 0 : b0 + 1, b2 = b1 == 2 ? 0 : b1 + 1;
+        const Pos nx2 = advance(nx1);
+        bool m1;
+        int32_t g1;
+        sub_mask(nx1, m1, g1);                 // before the window of t + 2 may replace it
+        const bool more = t + 2 < total;
+        if (more) load_sub(nx2, b2);           // buffer b2 was last read before the previous barrier
+        if constexpr (S) {
+          products(b0, opnd);
+          scores(b1, sp);
+          probs(b1, sp);
+          hand_over(b1, (t + 1) & 1, m1, g1, sp, opnd);
+        } else {
+          take_over(t & 1, sp, opnd);
+          products(b0, opnd);
+          scores(b1, sp);
+        }
+        if (more) store_sub(b2);
+        // sub-tile t + 2 has landed and is staged; P of t + 1 is in LDS; buffer b0 is free
+        asm volatile("s_waitcnt vmcnt(0)\n\ts_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+        nx1 = nx2;
+        b0 = b1;
+      }
+      if constexpr (!S) take_over((total - 1) & 1, sp, opnd);
+      products(b0, opnd);
+    } else {
+      // Two buffers: sub-tile t + 1 moves into the buffer of t - 1 while the products of t run.
+      for (int t = 0; t + 1 < total; ++t) {
+        const int b0 = t & 1, b1 = b0 ^ 1;
+        bool m1;
+        int32_t g1;
+        load_sub(nx1, b1);
+        sub_mask(nx1, m1, g1);
+        if constexpr (!S) take_over(0, sp, opnd);
+        products(b0, opnd);
+        store_sub(b1);
+        asm volatile("s_waitcnt vmcnt(0)\n\ts_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+        scores(b1, sp);
+        if constexpr (S) {
+          probs(b1, sp);
+          hand_over(b1, 0, m1, g1, sp, opnd);
+        }
+        hsap_lds_barrier();  // P of t + 1 is in LDS; every read of buffer b0 is done
+        nx1 = advance(nx1);
+      }
+      if constexpr (!S) take_over(0, sp, opnd);
+      products((total - 1) & 1, opnd);
+    }
+
+    // the accumulators to LDS, once no wave reads the ring or P any more
+    hsap_lds_barrier();
+    float* const mine = (float*)raw + w * 32 * ACC_STRIDE;
+    const float mul = S ? 1.f : a.scale;
 #pragma unroll
-  for (int mb = 0; mb < MB; ++mb)
+    for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
-    for (int j = 0; j < 16; ++j) {
-      const int64_t idx = ((kvrow + 32 * kb + c_row(j, hi)) * a.hkv + g) * D + 32 * mb + l32;
-      const float val = acc[mb][j] * mul;
-      if (BF16OUT) {
-        (s_wave ? a.dv16 : a.dk16)[idx] = (__bf16)val;
+      for (int j = 0; j < 16; ++j) mine[c_row(j, hi) * ACC_STRIDE + 32 * mb + l32] = acc[mb][j] * mul;
+    hsap_lds_barrier();
+  };
+  if (s_wave) work(std::true_type{});
+  else work(std::false_type{});
+
+  // whole rows out: this workgroup owns rows [krow0, krow0 + 32 KB) of chunk c for K/V head g,
+  // summed over the streams in order, 8 values per thread
+  constexpr int OUT = 2 * 32 * KB * CPR;  // 8-value pieces: dV rows, then dK rows
+#pragma unroll
+  for (int i0 = 0; i0 < OUT; i0 += 512) {
+    const int i = i0 + tid;
+    if (OUT % 512 != 0 && i >= OUT) break;
+    const int tensor = i / (32 * KB * CPR), r = i / CPR % (32 * KB), col = 8 * (i % CPR);
+    const float* src = (const float*)raw + ((4 * tensor + r / 32) * 32 + (r & 31)) * ACC_STRIDE + col;
+    f32x4 lo = *(const f32x4*)src, up = *(const f32x4*)(src + 4);
+#pragma unroll
+    for (int s = 1; s < QS; ++s) {
+      lo += *(const f32x4*)(src + s * KB * 32 * ACC_STRIDE);
+      up += *(const f32x4*)(src + s * KB * 32 * ACC_STRIDE + 4);
+    }
+    const int64_t idx = ((kvrow + r) * a.hkv + g) * D + col;
+    if constexpr (BF16OUT) {
+      __bf16* dst = (tensor ? a.dk16 : a.dv16) + idx;
+      const bf16x8 val{(__bf16)lo[0], (__bf16)lo[1], (__bf16)lo[2], (__bf16)lo[3],
+                       (__bf16)up[0], (__bf16)up[1], (__bf16)up[2], (__bf16)up[3]};
+      if (a.wide_kv) {
+        *(bf16x8*)dst = val;
       } else {
-        float* dst = s_wave ? a.dv : a.dk;
-        dst[idx] += val;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) dst[e] = val[e];
+      }
+    } else {
+      float* dst = (tensor ? a.dk : a.dv) + idx;
+      if (a.wide_kv) {
+        *(f32x4*)dst += lo;
+        *(f32x4*)(dst + 4) += up;
+      } else {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) dst[e] += e < 4 ? lo[e] : up[e - 4];
       }
     }
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -919,25 +824,36 @@ __global__ __launch_bounds__(64 * WAVES, 2) void attn_bwd_dq_kernel(BwdArgs a) {
     }
 }
 
-template <int D, int WAVES, bool BF16OUT, bool LIST = false>
-static hsap_status launch_dkdv(const BwdArgs& a, int64_t num_runs, hipStream_t stream) {
-  const int64_t blocks = num_runs * a.hkv;
+template <int D, int KB, bool BF16OUT, bool LIST>
+static hsap_status launch_dkdv_kb(BwdArgs a, int64_t num_runs, hipStream_t stream) {
+  a.parts = a.bn / (32 * KB);
+  const int64_t blocks = num_runs * a.parts * a.hkv;
   if (blocks > INT32_MAX) HSAP_FAIL(HSAP_ERR_INVALID_ARG, "too many runs x heads");
-  hipLaunchKernelGGL((attn_bwd_dkdv_kernel<D, WAVES, BF16OUT, LIST>), dim3((unsigned)blocks), dim3(64 * WAVES), 0,
-                     stream, a);
+  hipLaunchKernelGGL((attn_bwd_dkdv_kernel<D, KB, BF16OUT, LIST>), dim3((unsigned)blocks), dim3(512), 0, stream, a);
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) HSAP_FAIL(HSAP_ERR_HIP, "attn_bwd_dkdv launch: %s", hipGetErrorString(e));
   return HSAP_OK;
 }
 
-template <bool BF16OUT>
-static hsap_status launch_dkdv_split(const BwdArgs& a, int64_t num_runs, hipStream_t stream) {
-  const int64_t blocks = num_runs * a.hkv;
-  if (blocks > INT32_MAX) HSAP_FAIL(HSAP_ERR_INVALID_ARG, "too many runs x heads");
-  hipLaunchKernelGGL((attn_bwd_dkdv_split_kernel<BF16OUT>), dim3((unsigned)blocks), dim3(512), 0, stream, a);
-  const hipError_t e = hipGetLastError();
-  if (e != hipSuccess) HSAP_FAIL(HSAP_ERR_HIP, "attn_bwd_dkdv_split launch: %s", hipGetErrorString(e));
-  return HSAP_OK;
+// Key blocks of 32 per dK/dV workgroup, from the number of them in the whole call (one workgroup per
+// CU is resident, at head_dim 64 two of 64 keys).  Fewer key blocks per workgroup give more, shorter
+// workgroups at more staging traffic per product, which pays as long as they are at most about two
+// per CU.  Measured at one causal document, head_dim 128 (us for 128 / 64 / 32 keys per workgroup):
+// 512 blocks 111.9 / 84.1 / 62.4, 1024 blocks 115.4 / 98.9 / 120.2, 2048 blocks 152.3 / 194.2 / 247.3;
+// head_dim 64 (64 / 32 keys): 512 blocks 66.3 / 46.2, 1024 blocks 71.5 / 88.6.
+constexpr int64_t kDkdvComputeUnits = 256;
+
+template <bool BF16OUT, bool LIST = false>
+static hsap_status launch_dkdv(const BwdArgs& a, int d, int64_t num_runs, hipStream_t stream) {
+  const int64_t blocks = num_runs * (a.bn / 32) * a.hkv;
+  const bool one = blocks <= 2 * kDkdvComputeUnits;
+  if (d == 64) {
+    if (one) return launch_dkdv_kb<64, 1, BF16OUT, LIST>(a, num_runs, stream);
+    return launch_dkdv_kb<64, 2, BF16OUT, LIST>(a, num_runs, stream);
+  }
+  if (one) return launch_dkdv_kb<128, 1, BF16OUT, LIST>(a, num_runs, stream);
+  if (a.bn == 64 || blocks <= 4 * kDkdvComputeUnits) return launch_dkdv_kb<128, 2, BF16OUT, LIST>(a, num_runs, stream);
+  return launch_dkdv_kb<128, 4, BF16OUT, LIST>(a, num_runs, stream);
 }
 
 template <int D, int BN, int WAVES, bool BF16OUT, bool LIST = false>
@@ -1025,6 +941,8 @@ static hsap_status backward(const hsap_attn_desc* desc, const void* q, const voi
   a.hkv = desc->heads_kv;
   a.group = desc->heads_q / desc->heads_kv;
   a.bm = bm;
+  a.bn = bn;
+  a.wide_kv = (((uintptr_t)dk | (uintptr_t)dv) & 15) == 0;
   a.scale = desc->softmax_scale;
   a.scale_log2 = desc->softmax_scale * 1.44269504088896340736f;
   if (num_runs_q > 0) {
@@ -1049,9 +967,7 @@ static hsap_status backward(const hsap_attn_desc* desc, const void* q, const voi
   if (num_runs_k > 0) {
     a.tiles = tiles_k;
     a.runs = runs_k;
-    if (d == 128 && bn == 128) st = launch_dkdv_split<BF16OUT>(a, num_runs_k, s);
-    else if (d == 128) st = launch_dkdv<128, 2, BF16OUT>(a, num_runs_k, s);
-    else st = launch_dkdv<64, 2, BF16OUT>(a, num_runs_k, s);
+    st = launch_dkdv<BF16OUT>(a, d, num_runs_k, s);
     if (st != HSAP_OK) return st;
   }
   return HSAP_OK;
@@ -1099,6 +1015,8 @@ static hsap_status backward_tile_list(const hsap_attn_desc* desc, const void* q,
   a.hkv = desc->heads_kv;
   a.group = desc->heads_q / desc->heads_kv;
   a.bm = bm;
+  a.bn = bn;
+  a.wide_kv = (((uintptr_t)dk | (uintptr_t)dv) & 15) == 0;
   a.scale = desc->softmax_scale;
   a.scale_log2 = desc->softmax_scale * 1.44269504088896340736f;
   a.tiles = tiles;
@@ -1120,9 +1038,7 @@ static hsap_status backward_tile_list(const hsap_attn_desc* desc, const void* q,
   else HSAP_DQ_CASE(64, 64, 2)
 #undef HSAP_DQ_CASE
   if (st != HSAP_OK) return st;
-  if (d == 128 && bn == 128) return launch_dkdv<128, 4, false, true>(a, k_tiles, s);
-  if (d == 128) return launch_dkdv<128, 2, false, true>(a, k_tiles, s);
-  return launch_dkdv<64, 2, false, true>(a, k_tiles, s);
+  return launch_dkdv<false, true>(a, d, k_tiles, s);
 }
 
 }  // namespace hsap

@@ -1,0 +1,79 @@
+"""The dK/dV kernel's workgroup shapes (128, 64 or 32 keys, one, two or four streams of sub-tiles)
+against the fp64 oracle at the grid sizes where the choice changes and where a stream runs out."""
+import numpy as np
+import pytest
+import torch
+
+from _harness import Case, compare_backward
+from paper_2606_30460_amd.shard_attention import to_sharded
+
+pytestmark = pytest.mark.gpu
+
+CASES = [
+    # N, hq, hkv, d, bm, bn, document lengths (repeated to fill N); key blocks of 32 in the call
+    (2048, 8, 8, 128, 128, 128, [700]),     # 512: 32 keys per workgroup, four streams
+    (2048, 9, 9, 128, 128, 128, [700]),     # 576: 64 keys, two streams
+    (2048, 16, 16, 128, 256, 64, [333]),    # 1024, 64-key tiles
+    (4096, 18, 9, 128, 64, 128, [97, 5]),   # 1152: 128 keys, 64-row q-tiles, two query heads per K/V head
+    (2048, 18, 18, 128, 64, 64, [2048]),    # 1152, 64-key tiles
+    (2048, 8, 8, 64, 64, 64, [700]),        # head_dim 64: 512 and 576 blocks
+    (2048, 18, 9, 64, 128, 64, [41]),
+    (256, 3, 1, 128, 64, 128, [64]),        # runs of one 64-row q-tile per head: two sub-tiles, four streams
+    (128, 1, 1, 64, 64, 64, [128]),
+]
+
+
+def _case(N, hq, hkv, d, bm, bn, docs, seed=1):
+    lengths = []
+    while sum(lengths) < N:
+        lengths.append(docs[len(lengths) % len(docs)])
+    lengths[-1] -= sum(lengths) - N
+    cu = np.concatenate([[0], np.cumsum(lengths)]).astype(np.int32)
+    return Case(cu, N, 1, "contiguous", 0, hq, hkv, d, bm, bn, seed=seed, backward=True)
+
+
+@pytest.mark.parametrize("case", CASES)
+def test_backward_workgroup_shapes(case):
+    # bf16 gradients of the executor and fp32 accumulators of the tile-list call; the bar is what
+    # bf16 P, dS and results give: 2^-8 of the largest element, against the oracle in 64 bits
+    c = _case(*case)
+    ref = c.run_oracle()
+    for got in (c.run_executor(), c.run_tile_list()):
+        rep = compare_backward(got, ref)
+        assert max(rep.values()) <= 2.0 ** -7, (case, rep)
+        for key in ("dk", "dv"):
+            err = np.linalg.norm(got[key] - ref[key]) / np.linalg.norm(ref[key])
+            assert err <= 2.0 ** -7, (case, key, err)
+
+
+@pytest.mark.parametrize("case", [CASES[1], CASES[5]])
+def test_backward_unaligned_outputs(case):
+    # dK and dV 2 bytes (fp32 accumulators: 4 bytes) off a 16-byte boundary give the aligned bits
+    from paper_2606_30460_amd import _lib as L
+    c = _case(*case)
+    s = L.shard_desc(c.N, 1, "contiguous", 0, c.bm, c.bn)
+    desc = L.attn_desc(s, c.hq, c.hkv, c.d, c.d ** -0.5)
+    dev = torch.device("cuda")
+    q, k, v, d_o = (to_sharded(s, x.to(dev)).contiguous() for x in (c.q, c.k, c.v, c.do))
+    ex = L.Executor(desc, backward=True)
+    ex.plan(c.cu)
+    o, lse = torch.empty_like(q), torch.empty(c.hq, c.N, dtype=torch.float32, device=dev)
+    ex.forward(q, k, v, o, lse)
+    got = {}
+    for off in (0, 1):
+        dq = torch.empty_like(q)
+        dk, dv = (torch.zeros(k.numel() + off, dtype=k.dtype, device=dev)[off:].view(k.shape) for _ in range(2))
+        ex.backward(q, k, v, d_o, o, lse, dq, dk, dv)
+        delta = torch.empty_like(lse)
+        L.attn_bwd_preprocess(o, d_o, c.N, c.hq, c.d, delta)
+        doc_start = torch.empty(c.N, dtype=torch.int32, device=dev)
+        L.doc_start(torch.from_numpy(c.cu).to(dev), c.N, doc_start)
+        tiles = torch.from_numpy(L.plan(c.cu, s)["tiles"]).to(dev)
+        dqa = torch.zeros(q.shape, dtype=torch.float32, device=dev)
+        dka, dva = (torch.zeros(k.numel() + off, dtype=torch.float32, device=dev)[off:].view(k.shape) for _ in range(2))
+        L.partial_attn_bwd(desc, q, k, v, d_o, lse, delta, doc_start, tiles, dqa, dka, dva)
+        torch.cuda.synchronize()
+        got[off] = [x.clone() for x in (dk, dv, dka, dva)]
+    ex.close()
+    for a, b in zip(got[0], got[1]):
+        assert torch.equal(a, b)
