@@ -214,8 +214,7 @@ __global__ __launch_bounds__(512, D == 64 && KB == 2 ? 4 : 2) void attn_bwd_dkdv
     for (int k = 0; k < 2; ++k) troff[mb][k] = swz<CPR>(8 * k + tr_row, 32 * mb + tr_col) - 8 * k * D;
 
   const int nsub = a.bm / SUB;
-  const int subs = a.group * count * nsub;        // sub-tiles of the run, over the query heads
-  const int total = (subs + QS - 1) / QS;         // iterations: sub-tiles QS t + qs
+  const int total = (a.group * count * nsub + QS - 1) / QS;  // iterations over the streams' sub-tiles
   uint32_t win0 = 0u, win1 = 0u;
   int win_lo = 0, win_hi = -1;
   // The run's q-tiles, packed one per lane (q_tile | kind << 31) in windows of 64 tiles, read
@@ -244,34 +243,46 @@ __global__ __launch_bounds__(512, D == 64 && KB == 2 ? 4 : 2) void attn_bwd_dkdv
     win_hi = v;
   };
   // Sub-tile position as counters (no division in the loop): query head h, tile index idx in the
-  // run, SUB-row slice sb of the tile; left = sub-tiles behind this one.  A stream that has run out
-  // (its last iteration may lie past the end) repeats the run's last sub-tile with P = 0.
+  // run, SUB-row slice sb of the tile; with its position and kind once it has been loaded.  Stream qs
+  // takes the slices qs, qs + QS, ... of every tile or, of tiles with fewer slices (64-row q-tiles,
+  // four streams), slice qs % nsub of every other tile; there its last iteration may lie past the
+  // run's end, and then it repeats the last sub-tile with P = 0.
   struct Pos {
-    int h, idx, sb, left;
-    bool past;
+    int h, idx, sb;
+    bool past, masked;
+    int32_t gq0;
   };
-  auto advance = [&](Pos p) {
-#pragma unroll
-    for (int i = 0; i < QS; ++i) {
-      if (QS > 1 && p.left == 0) {
-        p.past = true;
-        break;
-      }
-      --p.left;
-      if (++p.sb == nsub) {
-        p.sb = 0;
-        if (++p.idx == count) {
-          p.idx = 0;
-          ++p.h;
-        }
+  auto fold = [&](Pos p) {  // tile indexes past the run's end continue with the next query head
+    if (p.idx >= count) {
+      p.idx -= count;
+      ++p.h;
+      if (QS > 2 && p.idx >= count) {
+        p.idx -= count;
+        ++p.h;
       }
     }
+    if (QS > 2 && p.h >= a.group) {
+      p.past = true;
+      p.h = a.group - 1;
+      p.idx = count - 1;
+    }
     return p;
+  };
+  auto advance = [&](Pos p) {
+    if (QS <= 2 || nsub >= QS) {  // (a q-tile has at least 64 rows: two slices of 32)
+      p.sb += QS;
+      if (p.sb >= nsub) {
+        p.sb -= nsub;
+        ++p.idx;
+      }
+    } else {
+      p.idx += QS / 2;
+    }
+    return fold(p);
   };
   auto tile_at = [&](const Pos& p) -> uint32_t {
     return __builtin_amdgcn_readlane(((p.idx >> 6) & 1) ? win1 : win0, p.idx & 63);
   };
-  auto q0_at = [&](uint32_t t, const Pos& p) { return (int64_t)(t & 0x7FFFFFFFu) * a.bm + p.sb * SUB; };
 
   // Q and dO sub-tiles by direct-to-LDS transfers: instruction u of the stream's wave x fills chunk
   // positions p = WCH x + 64 u + lane of the swizzled tile; the lane's source is the chunk the
@@ -311,19 +322,21 @@ __global__ __launch_bounds__(512, D == 64 && KB == 2 ? 4 : 2) void attn_bwd_dkdv
     const bool row_lane = S && kb == 0 && lane < SUB;  // this stream's lanes that bring the per-row values
     // the sub-tile's Q and dO into buffer buf (transfers), its LSE, delta and document starts into
     // registers of SUB lanes (written to LDS by store_sub)
-    auto load_sub = [&](const Pos& ps, int buf) {
+    auto load_sub = [&](Pos& ps, int buf) {
       // (uniform across the wave, which the transfers' scalar bases need the compiler to know)
       const int h = __builtin_amdgcn_readfirstlane(g * a.group + ps.h);
       ensure_window(ps.idx >> 6);
       const uint32_t t = tile_at(ps);
-      const int64_t q0 = __builtin_amdgcn_readfirstlane((int)q0_at(t, ps));
+      const int64_t q0 = __builtin_amdgcn_readfirstlane((int)(t & 0x7FFFFFFFu) * a.bm + ps.sb * SUB);
+      ps.masked = (t >> 31) != 0;
+      ps.gq0 = (int32_t)global_pos(a.geom, a.shard, q0);
       const int64_t base = (q0 * a.hq + h) * D;
       stage(a.q + base, q_tile(buf));
       stage(a.d_o + base, o_tile(buf));
       if (row_lane) {
         lreg = ps.past ? -__builtin_inff() : a.lse[(int64_t)h * n + q0 + lane];
         dreg = a.delta[(int64_t)h * n + q0 + lane];
-        sreg = a.doc_start[global_pos(a.geom, a.shard, q0) + lane];
+        sreg = a.doc_start[ps.gq0 + lane];
       }
     };
     auto store_sub = [&](int buf) {
@@ -374,9 +387,9 @@ __global__ __launch_bounds__(512, D == 64 && KB == 2 ? 4 : 2) void attn_bwd_dkdv
             sp[qb][4 * grp + e] = fast_exp2(__builtin_fmaf(sp[qb][4 * grp + e], a.scale_log2, -l4[e]));
         }
     };
-    auto hand_over = [&](int rb, int pbuf, bool masked, int32_t gq0, f32x16 (&sp)[QB], bf16x8 (&opnd)[QB][2])
+    auto hand_over = [&](int rb, int pbuf, const Pos& ps, f32x16 (&sp)[QB], bf16x8 (&opnd)[QB][2])
                          __attribute__((always_inline)) {
-      if (masked) {
+      if (ps.masked) {
 #pragma unroll
         for (int qb = 0; qb < QB; ++qb)
 #pragma unroll
@@ -385,7 +398,7 @@ __global__ __launch_bounds__(512, D == 64 && KB == 2 ? 4 : 2) void attn_bwd_dkdv
             const i32x4 s4 = *(const i32x4*)(&start_s[qs][rb][q4]);
 #pragma unroll
             for (int e = 0; e < 4; ++e)
-              if ((uint32_t)(gk - s4[e]) > (uint32_t)(gq0 + q4 + e - s4[e])) sp[qb][4 * grp + e] = 0.f;
+              if ((uint32_t)(gk - s4[e]) > (uint32_t)(ps.gq0 + q4 + e - s4[e])) sp[qb][4 * grp + e] = 0.f;
           }
       }
 #pragma unroll
@@ -431,27 +444,15 @@ __global__ __launch_bounds__(512, D == 64 && KB == 2 ? 4 : 2) void attn_bwd_dkdv
           }
         }
     };
-    auto sub_mask = [&](const Pos& p, bool& masked, int32_t& gq0) {
-      const uint32_t t = tile_at(p);
-      masked = (t >> 31) != 0;
-      gq0 = (int32_t)global_pos(a.geom, a.shard, q0_at(t, p));
-    };
-
     // prologue: the first sub-tiles staged, the scores of sub-tile 0
     ensure_window(0);
-    Pos cur{0, 0, 0, subs - 1, false};
-    if constexpr (QS > 1) {  // stream qs starts qs sub-tiles in
-      cur.past = qs >= subs;
-      const int i = min(qs, subs - 1);
-      cur.left = subs - 1 - i;
-      cur.sb = i % nsub;
-      cur.idx = i / nsub % count;
-      cur.h = i / nsub / count;
+    Pos cur{0, 0, qs, false, false, 0};
+    if (QS > 2 && nsub < QS) {
+      cur.sb = qs % 2;
+      cur.idx = qs / 2;
+      cur = fold(cur);
     }
     Pos nx1 = advance(cur);
-    bool m0;
-    int32_t g0;
-    sub_mask(cur, m0, g0);
     load_sub(cur, 0);
     store_sub(0);
     if (RING == 3 && total > 1) {
@@ -470,7 +471,7 @@ __global__ __launch_bounds__(512, D == 64 && KB == 2 ? 4 : 2) void attn_bwd_dkdv
     scores(0, sp);
     if constexpr (S) {
       probs(0, sp);
-      hand_over(0, 0, m0, g0, sp, opnd);
+      hand_over(0, 0, cur, sp, opnd);
     }
     hsap_lds_barrier();  // P of sub-tile 0 is in LDS
 
@@ -480,17 +481,14 @@ __global__ __launch_bounds__(512, D == 64 && KB == 2 ? 4 : 2) void attn_bwd_dkdv
       int b0 = 0;  // t % 3
       for (int t = 0; t + 1 < total; ++t) {
         const int b1 = b0 == 2 ? 0 : b0 + 1, b2 = b1 == 2 ? 0 : b1 + 1;
-        const Pos nx2 = advance(nx1);
-        bool m1;
-        int32_t g1;
-        sub_mask(nx1, m1, g1);                 // before the window of t + 2 may replace it
+        Pos nx2 = advance(nx1);
         const bool more = t + 2 < total;
-        if (more) load_sub(nx2, b2);           // buffer b2 was last read before the previous barrier
+        if (more) load_sub(nx2, b2);  // buffer b2 was last read before the previous barrier
         if constexpr (S) {
           products(b0, opnd);
           scores(b1, sp);
           probs(b1, sp);
-          hand_over(b1, (t + 1) & 1, m1, g1, sp, opnd);
+          hand_over(b1, (t + 1) & 1, nx1, sp, opnd);
         } else {
           // dS leaves sp, so the dP products of t + 1 go first: their row reads and the dS
           // arithmetic fill the shadow of the S wave's products, and dK follows (against dK first:
@@ -511,10 +509,7 @@ __global__ __launch_bounds__(512, D == 64 && KB == 2 ? 4 : 2) void attn_bwd_dkdv
       // Two buffers: sub-tile t + 1 moves into the buffer of t - 1 while the products of t run.
       for (int t = 0; t + 1 < total; ++t) {
         const int b0 = t & 1, b1 = b0 ^ 1;
-        bool m1;
-        int32_t g1;
         load_sub(nx1, b1);
-        sub_mask(nx1, m1, g1);
         if constexpr (!S) take_over(0, sp, opnd);
         products(b0, opnd);
         store_sub(b1);
@@ -522,7 +517,7 @@ __global__ __launch_bounds__(512, D == 64 && KB == 2 ? 4 : 2) void attn_bwd_dkdv
         scores(b1, sp);
         if constexpr (S) {
           probs(b1, sp);
-          hand_over(b1, 0, m1, g1, sp, opnd);
+          hand_over(b1, 0, nx1, sp, opnd);
         }
         hsap_lds_barrier();  // P of t + 1 is in LDS; every read of buffer b0 is done
         nx1 = advance(nx1);
