@@ -446,12 +446,9 @@ def fwd_source_hash() -> str:
 
 
 def fwd_kernel_name(res) -> str:
-    """The partial forward kernel the library dispatches for a workload's shapes (bf16 scores):
-    direct-to-LDS for head_dim 128 with 128- or 256-row q-tiles, register-staged otherwise."""
+    """The partial forward kernel the library dispatches for a workload's shapes (bf16 scores)."""
     d, bm, bn = res["head_dim"], res["block_m"], res["block_n"]
-    if d == 128 and bm in (128, 256):
-        return "attn_fwd_dl_kernel<%d, %d, false, false, false>" % (bn, bm // 32)
-    return "attn_fwd_kernel<%d, %d, %d, false, false, false>" % (d, bn, bm // 32)
+    return "attn_fwd_dl_kernel<%d, %d, %d, false, false, false>" % (d, bn, bm // 32)
 
 
 def bwd_kernel_names(res) -> list:

@@ -424,13 +424,13 @@ __global__ __launch_bounds__(64 * WAVES, 2) void attn_fwd_kernel(FwdArgs a) {
 }
 
 // ---------------------------------------------------------------------------
-// Direct-to-LDS forward for d = 128: WAVES waves (wave w owns query rows
-// 32w..32w+31; BM = 32 WAVES).  K and V steps go from global memory straight
+// Direct-to-LDS forward: WAVES waves (wave w owns query rows 32w..32w+31;
+// BM = 32 WAVES).  K and V steps go from global memory straight
 // into LDS (global_load_lds, no staging registers) in a ring of unpadded
-// XOR-swizzled [64][128] tiles.  Eight waves (BM = 256, one workgroup per CU):
+// XOR-swizzled [64][D] tiles.  Eight waves (BM = 256, one workgroup per CU):
 // three slots, K three steps ahead of its use in the scores and V two ahead of
-// its use in PV, so a transfer has two steps to arrive.  Four waves (BM = 128,
-// two workgroups per CU in 2 x 64 KB of LDS): two slots, K two steps ahead and
+// its use in PV, so a transfer has two steps to arrive.  Four waves or two (BM = 128, 64;
+// head_dim 128: two workgroups per CU in 2 x 64 KB of LDS): two slots, K two steps ahead and
 // V one, so a transfer has one step.  Each wave moves 1024 / WAVES of a tile's
 // 1024 16-byte chunks, 64 per instruction; a lane's source chunk is the one
 // the swizzle places at its destination.
@@ -444,15 +444,22 @@ __global__ __launch_bounds__(64 * WAVES, 2) void attn_fwd_kernel(FwdArgs a) {
 // its transfers and row maximum meanwhile.  Every step forms the next
 // step's scores; the last step's read a slot that no transfer is writing and
 // are dropped.
+//
+// head_dim 64 is bound by its vector instructions (148 per 64-key step and wave beside 16 MFMAs:
+// VALU busy 0.78, MFMA 0.50 at the 1.8 GHz the chip holds there): one score array instead of two
+// lets three waves share a SIMD.  One 65536-token document, 8192 rows x 16 heads: 1407 us with
+// register staging -> 1170 us (940 TFLOP/s); two waves per SIMD measure the same, four spill
+// (1400 us).  Two waves (64-row q-tiles) at head_dim 128, 20224 rows x 36 heads fused: 4.95 -> 4.25 ms.
 // ---------------------------------------------------------------------------
 // FP8: Q and K are e4m3 codes (scores from the 32x32x64 fp8 MFMA times q_scale[h] *
 // k_scale[chunk, g]); K tiles are [64][128 bytes], swizzled over their 8 chunks per row.
-template <int BN, int WAVES, bool FUSED, bool FP8 = false, bool LIST = false>
-__global__ __launch_bounds__(64 * WAVES, 2) void attn_fwd_dl_kernel(FwdArgs a) {
-  static_assert(WAVES == 4 || WAVES == 8, "four or eight waves");
+template <int D, int BN, int WAVES, bool FUSED, bool FP8 = false, bool LIST = false>
+__global__ __launch_bounds__(64 * WAVES, D == 64 ? 3 : 2) void attn_fwd_dl_kernel(FwdArgs a) {
+  static_assert(WAVES == 2 || WAVES == 4 || WAVES == 8, "two, four or eight waves");
+  static_assert(D == 128 || (D == 64 && !FP8), "head_dim 128, or 64 with bf16 scores");
   static_assert(!LIST || (!FUSED && !FP8), "the tile-list mode is the bf16 partial forward's");
   using KT = std::conditional_t<FP8, uint8_t, __bf16>;  // K element
-  constexpr int D = 128, KB = 64, SUBS = BN / KB, CPR = D / 8, TILE = KB * D;
+  constexpr int KB = 64, SUBS = BN / KB, CPR = D / 8, TILE = KB * D;
   constexpr int KCPR = D * (int)sizeof(KT) / 16;        // 16-byte chunks per K row
   constexpr int NSLOT = WAVES == 8 ? 3 : 2;  // ring depth
   constexpr int WCH = TILE / 8 / WAVES;      // 16-byte chunks of a V tile a wave moves
@@ -549,8 +556,8 @@ __global__ __launch_bounds__(64 * WAVES, 2) void attn_fwd_dl_kernel(FwdArgs a) {
   uint32_t gsrc[U], gsrck[UK];
 #pragma unroll
   for (int u = 0; u < U; ++u) {
-    const int p = WCH * w + 64 * u + lane, row = p >> 4;
-    gsrc[u] = (uint32_t)((row * rstride + swz_chunk<CPR>(row, p & 15) * 8) * 2);
+    const int p = WCH * w + 64 * u + lane, row = p / CPR;
+    gsrc[u] = (uint32_t)((row * rstride + swz_chunk<CPR>(row, p % CPR) * 8) * 2);
   }
 #pragma unroll
   for (int u = 0; u < UK; ++u) {
@@ -641,7 +648,8 @@ __global__ __launch_bounds__(64 * WAVES, 2) void attn_fwd_dl_kernel(FwdArgs a) {
   const uint32_t span = (uint32_t)(gq - qstart);
 
   int sk = 0;  // s % NSLOT
-  // Instruction order asked of the compiler for the block of a step (bf16 scores): four K-operand
+  // Instruction order asked of the compiler for the block of a step (head_dim 128, bf16 scores; at
+  // head_dim 64, bound by its vector instructions, such orders measured 0 to -1 %): four K-operand
   // reads ahead, then per score MFMA one LDS read and four vector instructions (the exponentials,
   // sums and conversions of this step), then per PV MFMA two V^T reads and three vector ones.
   auto block_order = []() __attribute__((always_inline)) {
@@ -754,7 +762,7 @@ __global__ __launch_bounds__(64 * WAVES, 2) void attn_fwd_dl_kernel(FwdArgs a) {
             o[mb] = mfma32(av, pb[nb][half], o[mb]);
           }
         }
-      if constexpr (!FP8) block_order();
+      if constexpr (D == 128 && !FP8) block_order();
       __builtin_amdgcn_s_setprio(0);
     } else {
       scores(Ks[s1], sn);
@@ -772,10 +780,19 @@ __global__ __launch_bounds__(64 * WAVES, 2) void attn_fwd_dl_kernel(FwdArgs a) {
     }
     sk = s1;
   };
-  f32x16 sn[KB / 32];
-  for (int s = 0; s < total; s += 2) {
-    step(s, std::integral_constant<int, 0>{}, sc, sn);
-    if (s + 1 < total) step(s + 1, std::integral_constant<int, 1>{}, sn, sc);
+  if constexpr (D == 64) {
+    // one score array: each 32-key half is replaced once its exponentials are formed (fewer registers,
+    // more waves per SIMD)
+    for (int s = 0; s < total; s += 2) {
+      step(s, std::integral_constant<int, 0>{}, sc, sc);
+      if (s + 1 < total) step(s + 1, std::integral_constant<int, 1>{}, sc, sc);
+    }
+  } else {
+    f32x16 sn[KB / 32];
+    for (int s = 0; s < total; s += 2) {
+      step(s, std::integral_constant<int, 0>{}, sc, sn);
+      if (s + 1 < total) step(s + 1, std::integral_constant<int, 1>{}, sn, sc);
+    }
   }
 
   l_run = pair_sum(l_run);
@@ -806,20 +823,20 @@ __global__ __launch_bounds__(64 * WAVES, 2) void attn_fwd_dl_kernel(FwdArgs a) {
   }
 }
 
-template <int BN, int WAVES, bool FUSED, bool FP8 = false>
+template <int D, int BN, int WAVES, bool FUSED, bool FP8 = false>
 static hsap_status launch_dl(const FwdArgs& a, int64_t num_runs, hipStream_t stream) {
   const int64_t blocks = num_runs * a.hq;
   if (blocks > INT32_MAX) HSAP_FAIL(HSAP_ERR_INVALID_ARG, "too many runs x heads");
   if constexpr (!FUSED && !FP8) {
     if (!a.runs) {
-      hipLaunchKernelGGL((attn_fwd_dl_kernel<BN, WAVES, false, false, true>), dim3((unsigned)blocks), dim3(64 * WAVES),
+      hipLaunchKernelGGL((attn_fwd_dl_kernel<D, BN, WAVES, false, false, true>), dim3((unsigned)blocks), dim3(64 * WAVES),
                          0, stream, a);
       const hipError_t e = hipGetLastError();
       if (e != hipSuccess) HSAP_FAIL(HSAP_ERR_HIP, "attn_fwd launch: %s", hipGetErrorString(e));
       return HSAP_OK;
     }
   }
-  hipLaunchKernelGGL((attn_fwd_dl_kernel<BN, WAVES, FUSED, FP8>), dim3((unsigned)blocks), dim3(64 * WAVES), 0, stream,
+  hipLaunchKernelGGL((attn_fwd_dl_kernel<D, BN, WAVES, FUSED, FP8>), dim3((unsigned)blocks), dim3(64 * WAVES), 0, stream,
                      a);
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) HSAP_FAIL(HSAP_ERR_HIP, "attn_fwd launch: %s", hipGetErrorString(e));
@@ -883,15 +900,15 @@ static hsap_status forward(const hsap_attn_desc* desc, const void* q, const void
   a.hkv = desc->heads_kv;
   a.group = desc->heads_q / desc->heads_kv;
   a.scale_log2 = desc->softmax_scale * 1.44269504088896340736f;
-  // head_dim 128 with 128- or 256-row q-tiles: the direct-to-LDS kernel, whose packed tile
-  // descriptors hold chunks below 256 and k-tiles below 2^23 (else the register-staged kernel)
-  const bool dl = d == 128 && (bm == 128 || bm == 256) && geom.P <= kMaxDlChunks && geom.n / bn < kMaxDlKTiles;
+  // the direct-to-LDS kernel's packed tile descriptors hold chunks below 256 and k-tiles below 2^23
+  // (else, and for fp8 scores with 64-row q-tiles, the register-staged kernel)
+  const bool packed = geom.P <= kMaxDlChunks && geom.n / bn < kMaxDlKTiles;
   if constexpr (FP8) {
     if ((uintptr_t)q & 15 || (uintptr_t)k & 15) HSAP_FAIL(HSAP_ERR_INVALID_ARG, "fp8 q and k must be 16-byte aligned");
-    if (dl && bm == 256)
-      return bn == 128 ? launch_dl<128, 8, FUSED, true>(a, num_runs, s) : launch_dl<64, 8, FUSED, true>(a, num_runs, s);
-    if (dl && bm == 128)
-      return bn == 128 ? launch_dl<128, 4, FUSED, true>(a, num_runs, s) : launch_dl<64, 4, FUSED, true>(a, num_runs, s);
+    if (packed && bm == 256)
+      return bn == 128 ? launch_dl<128, 128, 8, FUSED, true>(a, num_runs, s) : launch_dl<128, 64, 8, FUSED, true>(a, num_runs, s);
+    if (packed && bm == 128)
+      return bn == 128 ? launch_dl<128, 128, 4, FUSED, true>(a, num_runs, s) : launch_dl<128, 64, 4, FUSED, true>(a, num_runs, s);
     const int w = bm / 32;
     if (bn == 128) return w == 2 ? launch<128, 128, 2, FUSED, true>(a, num_runs, s)
                         : w == 4 ? launch<128, 128, 4, FUSED, true>(a, num_runs, s)
@@ -901,12 +918,11 @@ static hsap_status forward(const hsap_attn_desc* desc, const void* q, const void
                   : launch<128, 64, 8, FUSED, true>(a, num_runs, s);
   } else {
 #define HSAP_FWD_CASE(D_, BN_, W_) \
-  if (d == D_ && bn == BN_ && bm == 32 * W_) return launch<D_, BN_, W_, FUSED>(a, num_runs, s);
-  if (dl && bm == 256)
-    return bn == 128 ? launch_dl<128, 8, FUSED>(a, num_runs, s) : launch_dl<64, 8, FUSED>(a, num_runs, s);
-  if (dl && bm == 128)
-    return bn == 128 ? launch_dl<128, 4, FUSED>(a, num_runs, s) : launch_dl<64, 4, FUSED>(a, num_runs, s);
-  if (d == 128 && bm == 256)
+  if (d == D_ && bn == BN_ && bm == 32 * W_) \
+    return packed ? launch_dl<D_, BN_, W_, FUSED>(a, num_runs, s) : launch<D_, BN_, W_, FUSED>(a, num_runs, s);
+  if (packed && bm == 256)
+    return bn == 128 ? launch_dl<128, 128, 8, FUSED>(a, num_runs, s) : launch_dl<128, 64, 8, FUSED>(a, num_runs, s);
+  if (bm == 256)
     HSAP_FAIL(HSAP_ERR_UNSUPPORTED, "256-row q-tiles need sp_degree <= %d and fewer than 2^23 k-tiles per chunk",
               kMaxDlChunks);
   HSAP_FWD_CASE(128, 128, 4)
@@ -937,12 +953,14 @@ int fwd_resident_per_cu(const hsap_attn_desc* desc) {
   if (check_attn(desc, &geom) != HSAP_OK) return 0;
   const int bm = desc->shard.block_m, bn = desc->shard.block_n, d = desc->head_dim;
   if (bn != 64 && bn != 128) return 0;
-  const bool dl = d == 128 && (bm == 128 || bm == 256) && geom.P <= kMaxDlChunks && geom.n / bn < kMaxDlKTiles;
-  if (dl && bm == 256)
-    return bn == 128 ? blocks_per_cu(attn_fwd_dl_kernel<128, 8, false>, 512) : blocks_per_cu(attn_fwd_dl_kernel<64, 8, false>, 512);
-  if (dl) return bn == 128 ? blocks_per_cu(attn_fwd_dl_kernel<128, 4, false>, 256) : blocks_per_cu(attn_fwd_dl_kernel<64, 4, false>, 256);
+  const bool packed = geom.P <= kMaxDlChunks && geom.n / bn < kMaxDlKTiles;
+  if (packed && d == 128 && bm == 256)
+    return bn == 128 ? blocks_per_cu(attn_fwd_dl_kernel<128, 128, 8, false>, 512)
+                     : blocks_per_cu(attn_fwd_dl_kernel<128, 64, 8, false>, 512);
 #define HSAP_OCC_CASE(D_, BN_, W_) \
-  if (d == D_ && bn == BN_ && bm == 32 * W_) return blocks_per_cu(attn_fwd_kernel<D_, BN_, W_, false>, 64 * W_);
+  if (d == D_ && bn == BN_ && bm == 32 * W_) \
+    return packed ? blocks_per_cu(attn_fwd_dl_kernel<D_, BN_, W_, false>, 64 * W_) \
+                  : blocks_per_cu(attn_fwd_kernel<D_, BN_, W_, false>, 64 * W_);
   HSAP_OCC_CASE(128, 128, 4)
   HSAP_OCC_CASE(128, 64, 4)
   HSAP_OCC_CASE(128, 128, 2)
