@@ -330,31 +330,58 @@ __device__ inline float block_max_256(float v, float* part) {
   return fmaxf(fmaxf(part[0], part[1]), fmaxf(part[2], part[3]));
 }
 
+// Calls f(element offset, 8 values) for this thread's 16-byte chunks of a range, QU of them read before
+// the first is used.  Both passes are bound by HBM; with four loads in flight per thread and the second
+// pass in reverse (below), 8 x 4096 rows x 32 heads of 128 (268 MB read twice, 134 MB written) take
+// 136 -> 120 us, 4096 rows of 96 heads (a quarter of that) 22.7 -> 20.8 us; neighbouring heads per
+// workgroup (longer contiguous pieces) and slices' two passes interleaved in one launch gave nothing.
+constexpr int QU = 4;
+
+template <typename F>
+__device__ __forceinline__ void quant_chunks(const QuantArgs& a, const QuantRange& q, F f) {
+  int64_t i = q.c0 + threadIdx.x;
+  for (; i + 256 * (QU - 1) < q.c1; i += 256 * QU) {
+    int64_t o[QU];
+    bf16x8 v[QU];
+#pragma unroll
+    for (int u = 0; u < QU; ++u) {
+      o[u] = q.offset(a, i + 256 * u);
+      v[u] = *(const bf16x8*)(a.x + o[u]);
+    }
+#pragma unroll
+    for (int u = 0; u < QU; ++u) f(o[u], v[u]);
+  }
+  for (; i < q.c1; i += 256) {
+    const int64_t o = q.offset(a, i);
+    f(o, *(const bf16x8*)(a.x + o));
+  }
+}
+
 __global__ __launch_bounds__(256) void quantize_amax_kernel(QuantArgs a) {
   __shared__ float part[4];
   const int gh = blockIdx.x / QSPLIT, sp = blockIdx.x - gh * QSPLIT;
   const QuantRange q(a, gh, sp);
   float amax = 0.f;
-  for (int64_t i = q.c0 + threadIdx.x; i < q.c1; i += 256) {
-    const bf16x8 v = *(const bf16x8*)(a.x + q.offset(a, i));
+  quant_chunks(a, q, [&](int64_t, const bf16x8& v) {
 #pragma unroll
     for (int e = 0; e < 8; ++e) amax = fmaxf(amax, fabsf((float)v[e]));
-  }
+  });
   amax = block_max_256(amax, part);
   if (threadIdx.x == 0) a.partial[blockIdx.x] = amax;
 }
 
+// The workgroups run in the opposite order of the first pass, eight at a time (a range stays on its XCD:
+// the grid is a multiple of QSPLIT): what that pass read last is what the caches still hold.
 __global__ __launch_bounds__(256) void quantize_convert_kernel(QuantArgs a) {
-  const int gh = blockIdx.x / QSPLIT, sp = blockIdx.x - gh * QSPLIT;
+  const int block = ((int)gridDim.x - 8 - (int)(blockIdx.x & ~7u)) + (int)(blockIdx.x & 7);
+  const int gh = block / QSPLIT, sp = block - gh * QSPLIT;
   float amax = 0.f;
 #pragma unroll
   for (int i = 0; i < QSPLIT; ++i) amax = fmaxf(amax, a.partial[gh * QSPLIT + i]);
   const float inv = amax > 0.f ? 448.f / amax : 0.f;
   if (sp == 0 && threadIdx.x == 0) a.scale[gh] = amax > 0.f ? amax / 448.f : 0.f;
   const QuantRange q(a, gh, sp);
-  for (int64_t i = q.c0 + threadIdx.x; i < q.c1; i += 256) {
-    const int64_t o = q.offset(a, i);
-    const bf16x8 v = *(const bf16x8*)(a.x + o);
+  quant_chunks(a, q, [&](int64_t o, const bf16x8& v) {
     float y[8];
 #pragma unroll
     for (int e = 0; e < 8; ++e) y[e] = fminf(fmaxf((float)v[e] * inv, -448.f), 448.f);
@@ -364,7 +391,7 @@ __global__ __launch_bounds__(256) void quantize_convert_kernel(QuantArgs a) {
     hi = __builtin_amdgcn_cvt_pk_fp8_f32(y[4], y[5], hi, false);
     hi = __builtin_amdgcn_cvt_pk_fp8_f32(y[6], y[7], hi, true);
     *(uint2*)(a.out + o) = make_uint2((uint32_t)lo, (uint32_t)hi);
-  }
+  });
 }
 
 static hsap_status check_launch(const char* what) {

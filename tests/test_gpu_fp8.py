@@ -158,3 +158,16 @@ def test_fp8_forward_zero_slices(bm):
         rep = {"o": max_abs(o, ref["o"]), "lse": max_abs(lse, ref["lse"])}
         _say("zero slices, shard", r, rep)
         assert rep["o"] <= O_ATOL and rep["lse"] <= LSE_ATOL, (r, rep)
+
+
+@pytest.mark.parametrize("shape", [(2, 4129, 3, 128), (1, 2049, 5, 64), (5, 2100, 1, 24), (1, 16421, 1, 128)])
+def test_quantize_row_range_remainders(shape):
+    # row ranges whose chunks are whole, partial and odd multiples of what a workgroup reads at once
+    g = torch.Generator().manual_seed(shape[1])
+    x = torch.randn(shape, generator=g).to(torch.bfloat16)
+    x[0, -1, 0, -1] = 300.0        # the slice's largest value in its last row
+    codes, scale = _quantize(x.cuda())
+    torch.cuda.synchronize()
+    ref_codes, ref_scale = oracle.quantize_fp8(x.float().numpy())
+    assert np.array_equal(codes.cpu().numpy(), ref_codes)
+    assert np.array_equal(scale.cpu().numpy(), ref_scale)
