@@ -588,28 +588,37 @@ __global__ __launch_bounds__(512, D == 64 && KB == 2 ? 4 : 2) void attn_bwd_dkdv
 // A run may span several chunks (tile by tile), so one run per q-tile covers
 // every chunk; dQ stays in registers for the whole run and is written once at
 // the end, by the q-tile's only run: a plain read-add-write of the fp32
-// accumulator, or a store of the final bf16 value.
+// accumulator, or a store of the final bf16 value.  KS key streams (small grids,
+// key_streams()): WAVES x KS waves, stream ks with a ring and a sum of its own
+// over the steps ks, ks + KS, ..., added in LDS in stream order.
 // ---------------------------------------------------------------------------
-template <int D, int BN, int WAVES, bool BF16OUT, bool LIST = false>
-__global__ __launch_bounds__(64 * WAVES, 2) void attn_bwd_dq_kernel(BwdArgs a) {
+template <int D, int BN, int WAVES, bool BF16OUT, bool LIST = false, int KS = 1>
+__global__ __launch_bounds__(64 * WAVES * KS, 2) void attn_bwd_dq_kernel(BwdArgs a) {
   static_assert(!LIST || !BF16OUT, "the tile-list mode accumulates fp32");
   constexpr int KB = 64;                     // keys per step
   constexpr int SUBS = BN / KB;
-  constexpr int NT = 64 * WAVES;
   constexpr int CPR = D / 8;
   constexpr int MB = D / 32;
   constexpr int CHUNKS = KB * CPR;           // 16-byte chunks per K (or V) step
-  static_assert(CHUNKS % NT == 0, "step must split evenly over the threads");
+  static_assert(KS == 1 || WAVES * KS <= 8, "at most eight waves with key streams");
   constexpr float LOG2E = 1.44269504088896340736f;
   constexpr float NEG_INF = -__builtin_inff();
-  __shared__ __attribute__((aligned(16))) __bf16 Ks[2][KB * D];  // swizzled [key][d]
-  __shared__ __attribute__((aligned(16))) __bf16 Vs[2][KB * D];
+  // the streams' rings of swizzled [key][d] tiles; with several streams used again for their sums
+  constexpr int TILE = KB * D;
+  __shared__ __attribute__((aligned(16))) __bf16 rings[KS][4 * TILE];
 
   const int tid = threadIdx.x;
-  const int w = tid >> 6, lane = tid & 63, l32 = lane & 31, hi = lane >> 5;
+  const int lane = tid & 63, l32 = lane & 31, hi = lane >> 5;
+  // wave -> (32-row slice of the q-tile, key stream)
+  const int w = KS == 1 ? tid >> 6 : __builtin_amdgcn_readfirstlane(tid >> 6) % WAVES;
+  const int ks = KS == 1 ? 0 : __builtin_amdgcn_readfirstlane(tid >> 6) / WAVES;
+  auto Ks = [&](int slot) { return &rings[ks][slot * TILE]; };
+  auto Vs = [&](int slot) { return &rings[ks][(2 + slot) * TILE]; };
   int run_idx, h;
   run_and_head(blockIdx.x, a.hq, a.hkv, run_idx, h);
-  // LIST: the tile-list mode, this workgroup's q-tile found in one chunk's list
+  // LIST: the tile-list mode, this workgroup's q-tile found in one chunk's list (last q-tiles first:
+  // under the causal mask they have the most keys)
+  if (LIST) run_idx = (int)(a.geom.n / (32 * WAVES)) - 1 - run_idx;
   const hsap_run run = LIST ? q_tile_run(a.tiles, a.num_tiles, run_idx, lane) : a.runs[run_idx];
   const int g = h / a.group;
   const int64_t n = a.geom.n;
@@ -654,7 +663,7 @@ __global__ __launch_bounds__(64 * WAVES, 2) void attn_bwd_dq_kernel(BwdArgs a) {
 #pragma unroll
         for (int kk = 0; kk < wdt; ++kk) p[kk] = p[kk] + p[kk + wdt];
       dlt = p[0] + __shfl_xor(p[0], 32);
-      if (hi == 0) a.delta_out[(int64_t)h * n + qrow] = dlt;  // read by the dK/dV kernel, launched after
+      if (hi == 0 && ks == 0) a.delta_out[(int64_t)h * n + qrow] = dlt;  // read by the dK/dV kernel, launched after
     } else {
       dlt = a.delta[(int64_t)h * n + qrow];
     }
@@ -673,7 +682,10 @@ __global__ __launch_bounds__(64 * WAVES, 2) void attn_bwd_dq_kernel(BwdArgs a) {
     for (int k = 0; k < 2; ++k) troff[mb][k] = swz<CPR>(8 * k + tr_row, 32 * mb + tr_col) - 8 * k * D;
 
   const int64_t rstride = (int64_t)a.hkv * D;
-  const int total = run.count * SUBS;
+  // Stream ks takes the steps ks, ks + KS, ... of the run: its step i is the run's step KS i + ks.
+  const int run_steps = run.count * SUBS;
+  const int total = KS == 1 ? run_steps : (run_steps - ks + KS - 1) / KS;  // this stream's steps
+  auto at = [&](int i) { return KS == 1 ? i : KS * i + ks; };
   // The run's tile descriptors, packed one per lane (k_tile | chunk << 23 | kind << 31) in windows
   // of 64 tiles (window v in win0 or win1 by parity), read with v_readlane: the loop issues no
   // vector load besides the transfers (one would wait for every transfer in flight).
@@ -691,11 +703,11 @@ __global__ __launch_bounds__(64 * WAVES, 2) void attn_bwd_dq_kernel(BwdArgs a) {
     win_hi = v;
   };
   auto tile_at = [&](int s) -> uint32_t {
-    const int idx = s / SUBS;
+    const int idx = at(s) / SUBS;
     return __builtin_amdgcn_readlane(((idx >> 6) & 1) ? win1 : win0, idx & 63);
   };
   auto chunk_of = [](uint32_t p) { return (int32_t)((p >> 23) & 0xFFu); };
-  auto step_row0 = [&](uint32_t p, int s) { return (int64_t)(p & 0x7FFFFFu) * BN + (s % SUBS) * KB; };
+  auto step_row0 = [&](uint32_t p, int s) { return (int64_t)(p & 0x7FFFFFu) * BN + (at(s) % SUBS) * KB; };
   // the step's first row in the sharded K/V buffers: chunk of the tile, K/V head g
   auto step_off = [&](uint32_t p, int s) { return (((int64_t)chunk_of(p) * n + step_row0(p, s)) * a.hkv + g) * D; };
   load_window(0);
@@ -726,10 +738,10 @@ __global__ __launch_bounds__(64 * WAVES, 2) void attn_bwd_dq_kernel(BwdArgs a) {
 #pragma unroll
   for (int mb = 0; mb < MB; ++mb) dq[mb] = f32x16{};
 
-  {
+  if (KS == 1 || total > 0) {
     const int64_t off = step_off(tile_at(0), 0);
-    stage(a.k + off, Ks[0]);
-    stage(a.v + off, Vs[0]);
+    stage(a.k + off, Ks(0));
+    stage(a.v + off, Vs(0));
   }
   // The compiler does not see the waits inside asm statements: without a use of Q and dO here it
   // would wait for their loads at their first use inside the loop, in every step, and since the
@@ -742,15 +754,15 @@ __global__ __launch_bounds__(64 * WAVES, 2) void attn_bwd_dq_kernel(BwdArgs a) {
   // immediate); the next step's transfers go to the other slot
   auto step = [&](int s, auto par) __attribute__((always_inline)) {
     constexpr int PAR = decltype(par)::value;
-    if (s + 1 < total && ((s + 1) / SUBS) >> 6 > win_hi) load_window(win_hi + 1);
+    if (s + 1 < total && (at(s + 1) / SUBS) >> 6 > win_hi) load_window(win_hi + 1);
     const uint32_t tile = tile_at(s);
     if (s + 1 < total) {
       const int64_t off = step_off(tile_at(s + 1), s + 1);
-      stage(a.k + off, Ks[PAR ^ 1]);
-      stage(a.v + off, Vs[PAR ^ 1]);
+      stage(a.k + off, Ks(PAR ^ 1));
+      stage(a.v + off, Vs(PAR ^ 1));
     }
-    const __bf16* K = Ks[PAR];
-    const __bf16* V = Vs[PAR];
+    const __bf16* K = Ks(PAR);
+    const __bf16* V = Vs(PAR);
     // Masked tile: a step whose keys no query of the wave may see contributes nothing (skipped);
     // one whose keys every query of the wave may see needs no per-element mask.
     bool live = true, need_mask = false;
@@ -799,9 +811,42 @@ __global__ __launch_bounds__(64 * WAVES, 2) void attn_bwd_dq_kernel(BwdArgs a) {
     // every read of slot PAR is done and the transfers into slot PAR ^ 1 have landed
     asm volatile("s_waitcnt vmcnt(0)\n\ts_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
   };
-  for (int s = 0; s < total; s += 2) {
-    step(s, std::integral_constant<int, 0>{});
-    if (s + 1 < total) step(s + 1, std::integral_constant<int, 1>{});
+  if constexpr (KS == 1) {
+    for (int s = 0; s < total; s += 2) {
+      step(s, std::integral_constant<int, 0>{});
+      if (s + 1 < total) step(s + 1, std::integral_constant<int, 1>{});
+    }
+  } else {
+    // every stream takes part in the barriers of the longest one (the first)
+    const int most = (run_steps + KS - 1) / KS;
+    for (int s = 0; s < most; s += 2) {
+      if (s < total) step(s, std::integral_constant<int, 0>{});
+      else vm_wait_barrier<0>();
+      if (s + 1 < most) {
+        if (s + 1 < total) step(s + 1, std::integral_constant<int, 1>{});
+        else vm_wait_barrier<0>();
+      }
+    }
+    // the streams' sums to LDS (register by register; the loop ended with a barrier and no transfer is
+    // in flight), added in stream order
+    float* const res = (float*)rings;
+    static_assert(KS * 4 * TILE * 2 >= (KS - 1) * WAVES * (D / 2) * 256, "room for the streams' sums");
+    if (ks > 0) {
+      float* const mine = res + ((ks - 1) * WAVES + w) * (D / 2) * 64 + lane;
+#pragma unroll
+      for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+        for (int j = 0; j < 16; ++j) mine[(16 * mb + j) * 64] = dq[mb][j];
+    }
+    hsap_lds_barrier();
+    if (ks > 0) return;
+    for (int x = 1; x < KS; ++x) {
+      const float* const other = res + ((x - 1) * WAVES + w) * (D / 2) * 64 + lane;
+#pragma unroll
+      for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+        for (int j = 0; j < 16; ++j) dq[mb][j] += other[(16 * mb + j) * 64];
+    }
   }
 
   // dQ^T: this lane's query, d = 32 mb + 8 grp + 4 hi + e for register j = 4 grp + e
@@ -839,32 +884,40 @@ static hsap_status launch_dkdv_kb(BwdArgs a, int64_t num_runs, hipStream_t strea
 // per CU.  Measured at one causal document, head_dim 128 (us for 128 / 64 / 32 keys per workgroup):
 // 512 blocks 111.9 / 84.1 / 62.4, 1024 blocks 115.4 / 98.9 / 120.2, 2048 blocks 152.3 / 194.2 / 247.3;
 // head_dim 64 (64 / 32 keys): 512 blocks 66.3 / 46.2, 1024 blocks 71.5 / 88.6.
-constexpr int64_t kDkdvComputeUnits = 256;
-
 template <bool BF16OUT, bool LIST = false>
 static hsap_status launch_dkdv(const BwdArgs& a, int d, int64_t num_runs, hipStream_t stream) {
   const int64_t blocks = num_runs * (a.bn / 32) * a.hkv;
-  const bool one = blocks <= 2 * kDkdvComputeUnits;
+  const bool one = blocks <= 2 * kComputeUnits;
   if (d == 64) {
     if (one) return launch_dkdv_kb<64, 1, BF16OUT, LIST>(a, num_runs, stream);
     return launch_dkdv_kb<64, 2, BF16OUT, LIST>(a, num_runs, stream);
   }
   if (one) return launch_dkdv_kb<128, 1, BF16OUT, LIST>(a, num_runs, stream);
-  if (a.bn == 64 || blocks <= 4 * kDkdvComputeUnits) return launch_dkdv_kb<128, 2, BF16OUT, LIST>(a, num_runs, stream);
+  if (a.bn == 64 || blocks <= 4 * kComputeUnits) return launch_dkdv_kb<128, 2, BF16OUT, LIST>(a, num_runs, stream);
   return launch_dkdv_kb<128, 4, BF16OUT, LIST>(a, num_runs, stream);
 }
 
-template <int D, int BN, int WAVES, bool BF16OUT, bool LIST = false>
-static hsap_status launch_dq(const BwdArgs& a, int64_t num_runs, hipStream_t stream) {
+template <int D, int BN, int WAVES, bool BF16OUT, bool LIST, int KS>
+static hsap_status launch_dq_ks(const BwdArgs& a, int64_t num_runs, hipStream_t stream) {
   const int64_t blocks = num_runs * a.hq;
   if (blocks > INT32_MAX) HSAP_FAIL(HSAP_ERR_INVALID_ARG, "too many runs x heads");
-  hipLaunchKernelGGL((attn_bwd_dq_kernel<D, BN, WAVES, BF16OUT, LIST>), dim3((unsigned)blocks), dim3(64 * WAVES), 0,
-                     stream, a);
+  hipLaunchKernelGGL((attn_bwd_dq_kernel<D, BN, WAVES, BF16OUT, LIST, KS>), dim3((unsigned)blocks),
+                     dim3(64 * WAVES * KS), 0, stream, a);
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) HSAP_FAIL(HSAP_ERR_HIP, "attn_bwd_dq launch: %s", hipGetErrorString(e));
   return HSAP_OK;
 }
 
+template <int D, int BN, int WAVES, bool BF16OUT, bool LIST = false>
+static hsap_status launch_dq(const BwdArgs& a, int64_t num_runs, hipStream_t stream) {
+  if constexpr (WAVES < 8) {
+    const int ks = key_streams(D, 32 * WAVES, a.geom.n / (32 * WAVES) * a.hq);
+    if constexpr (D == 64 && WAVES == 2)
+      if (ks == 4) return launch_dq_ks<D, BN, WAVES, BF16OUT, LIST, 4>(a, num_runs, stream);
+    if (ks >= 2) return launch_dq_ks<D, BN, WAVES, BF16OUT, LIST, 2>(a, num_runs, stream);
+  }
+  return launch_dq_ks<D, BN, WAVES, BF16OUT, LIST, 1>(a, num_runs, stream);
+}
 
 // Packed tile descriptors of the dQ kernel: chunks below 256, k-tiles below 2^23.
 constexpr int kMaxDqChunks = 256;

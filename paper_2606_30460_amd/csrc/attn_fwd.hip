@@ -445,6 +445,10 @@ __global__ __launch_bounds__(64 * WAVES, 2) void attn_fwd_kernel(FwdArgs a) {
 // step's scores; the last step's read a slot that no transfer is writing and
 // are dropped.
 //
+// KS key streams (small grids, key_streams()): WAVES x KS waves, stream ks with a ring and a running
+// softmax of its own over the steps ks, ks + KS, ...; at the end the streams' O, maxima and sums are
+// combined in LDS in stream order.
+//
 // head_dim 64 is bound by its vector instructions (148 per 64-key step and wave beside 16 MFMAs:
 // VALU busy 0.78, MFMA 0.50 at the 1.8 GHz the chip holds there): one score array instead of two
 // lets three waves share a SIMD.  One 65536-token document, 8192 rows x 16 heads: 1407 us with
@@ -453,14 +457,15 @@ __global__ __launch_bounds__(64 * WAVES, 2) void attn_fwd_kernel(FwdArgs a) {
 // ---------------------------------------------------------------------------
 // FP8: Q and K are e4m3 codes (scores from the 32x32x64 fp8 MFMA times q_scale[h] *
 // k_scale[chunk, g]); K tiles are [64][128 bytes], swizzled over their 8 chunks per row.
-template <int D, int BN, int WAVES, bool FUSED, bool FP8 = false, bool LIST = false>
-__global__ __launch_bounds__(64 * WAVES, D == 64 ? 3 : 2) void attn_fwd_dl_kernel(FwdArgs a) {
+template <int D, int BN, int WAVES, bool FUSED, bool FP8 = false, bool LIST = false, int KS = 1>
+__global__ __launch_bounds__(64 * WAVES * KS, D == 64 && KS == 1 ? 3 : 2) void attn_fwd_dl_kernel(FwdArgs a) {
   static_assert(WAVES == 2 || WAVES == 4 || WAVES == 8, "two, four or eight waves");
   static_assert(D == 128 || (D == 64 && !FP8), "head_dim 128, or 64 with bf16 scores");
   static_assert(!LIST || (!FUSED && !FP8), "the tile-list mode is the bf16 partial forward's");
   using KT = std::conditional_t<FP8, uint8_t, __bf16>;  // K element
   constexpr int KB = 64, SUBS = BN / KB, CPR = D / 8, TILE = KB * D;
   constexpr int KCPR = D * (int)sizeof(KT) / 16;        // 16-byte chunks per K row
+  static_assert(KS == 1 || (WAVES * KS <= 8 && WAVES < 8), "at most eight waves with key streams");
   constexpr int NSLOT = WAVES == 8 ? 3 : 2;  // ring depth
   constexpr int WCH = TILE / 8 / WAVES;      // 16-byte chunks of a V tile a wave moves
   constexpr int U = WCH / 64;                // transfer instructions per wave per V tile
@@ -468,16 +473,25 @@ __global__ __launch_bounds__(64 * WAVES, D == 64 ? 3 : 2) void attn_fwd_dl_kerne
   static_assert(WCHK % 64 == 0, "a wave moves whole instructions of a K tile");
   constexpr float NEG_INF = -__builtin_inff();
   constexpr float RESCALE_SLACK = 8.f;
-  __shared__ __attribute__((aligned(16))) KT Ks[NSLOT][TILE];
-  __shared__ __attribute__((aligned(16))) __bf16 Vs[NSLOT][TILE];
+  // the streams' rings; with several streams used again for their results at the end
+  constexpr int K_BYTES = TILE * (int)sizeof(KT), STREAM_BYTES = NSLOT * (K_BYTES + TILE * 2);
+  static_assert(KS == 1 || KS * STREAM_BYTES >= (KS - 1) * WAVES * (D / 2 + 2) * 256, "room for the streams' results");
+  __shared__ __attribute__((aligned(16))) unsigned char rings[KS * STREAM_BYTES];
   __shared__ float kscale_s[FP8 ? kMaxDlChunks : 1];  // fp8: K scale of each chunk for this head's K/V head
   typedef __attribute__((address_space(3))) void* lds_void;
 
   const int tid = threadIdx.x;
-  const int w = tid >> 6, lane = tid & 63, l32 = lane & 31, hi = lane >> 5;
+  const int lane = tid & 63, l32 = lane & 31, hi = lane >> 5;
+  // wave -> (32-row slice of the q-tile, key stream)
+  const int w = KS == 1 ? tid >> 6 : __builtin_amdgcn_readfirstlane(tid >> 6) % WAVES;
+  const int ks = KS == 1 ? 0 : __builtin_amdgcn_readfirstlane(tid >> 6) / WAVES;
+  auto Ks = [&](int slot) { return (KT*)(rings + ks * STREAM_BYTES + slot * K_BYTES); };
+  auto Vs = [&](int slot) { return (__bf16*)(rings + ks * STREAM_BYTES + NSLOT * K_BYTES) + slot * TILE; };
   int run_idx, h;
   run_and_head(blockIdx.x, a.hq, a.hkv, run_idx, h);
   // LIST: the tile-list mode of the partial forward, this workgroup's q-tile found in one chunk's list
+  // (last q-tiles first: under the causal mask they have the most keys)
+  if (LIST) run_idx = (int)(a.geom.n / (32 * WAVES)) - 1 - run_idx;
   const hsap_run run = LIST ? q_tile_run(a.tiles, a.num_tiles, run_idx, lane) : a.runs[run_idx];
   const int slot = run.slot;
   const bool final_out = FUSED || (slot == kFinalSlot && a.o_out != nullptr);
@@ -518,9 +532,12 @@ __global__ __launch_bounds__(64 * WAVES, D == 64 ? 3 : 2) void attn_fwd_dl_kerne
   // here and visible after the prologue's barrier)
   const float head_scale = FP8 ? a.scale_log2 * a.q_scale[h] : a.scale_log2;
   if constexpr (FP8)
-    for (int c = tid; c < a.geom.P; c += 64 * WAVES) kscale_s[c] = a.k_scale[c * a.hkv + (h / a.group)];
+    for (int c = tid; c < a.geom.P; c += 64 * WAVES * KS) kscale_s[c] = a.k_scale[c * a.hkv + (h / a.group)];
   const int64_t rstride = (int64_t)a.hkv * D;
-  const int total = run.count * SUBS;
+  // Stream ks takes the steps ks, ks + KS, ... of the run: its step i is the run's step KS i + ks.
+  const int run_steps = run.count * SUBS;
+  const int total = KS == 1 ? run_steps : (run_steps - ks + KS - 1) / KS;  // this stream's steps
+  auto at = [&](int i) { return KS == 1 ? i : KS * i + ks; };
   // The run's tile descriptors, packed one per lane (k_tile | chunk << 23 | kind << 31) in
   // windows of 64 tiles (window v in win0 or win1 by parity), read with v_readlane: no memory
   // access for descriptors inside the loop (a vector load there would wait for every
@@ -539,13 +556,13 @@ __global__ __launch_bounds__(64 * WAVES, D == 64 ? 3 : 2) void attn_fwd_dl_kerne
     win_hi = v;
   };
   auto tile_at = [&](int s) -> uint32_t {
-    const int idx = s / SUBS;
+    const int idx = at(s) / SUBS;
     return __builtin_amdgcn_readlane(((idx >> 6) & 1) ? win1 : win0, idx & 63);
   };
   auto chunk_of = [](uint32_t p) { return (int32_t)((p >> 23) & 0xFFu); };
-  auto step_row0 = [&](uint32_t p, int s) { return (int64_t)(p & 0x7FFFFFu) * BN + (s % SUBS) * KB; };
+  auto step_row0 = [&](uint32_t p, int s) { return (int64_t)(p & 0x7FFFFFu) * BN + (at(s) % SUBS) * KB; };
   load_window(0);
-  const int64_t run_base = FUSED ? 0 : (((int64_t)chunk_of(tile_at(0)) * n) * a.hkv + g) * D;
+  const int64_t run_base = FUSED ? 0 : (((int64_t)chunk_of(__builtin_amdgcn_readlane(win0, 0)) * n) * a.hkv + g) * D;
   auto step_off = [&](uint32_t p, int s) {
     if (FUSED) return (((int64_t)chunk_of(p) * n + step_row0(p, s)) * a.hkv + g) * D;
     return run_base + step_row0(p, s) * rstride;
@@ -637,12 +654,12 @@ __global__ __launch_bounds__(64 * WAVES, D == 64 ? 3 : 2) void attn_fwd_dl_kerne
   for (int j = 0; j < NSLOT; ++j)
     if (j < total) {
       const uint32_t t = tile_at(j);
-      stage_k(kbase + step_off(t, j), Ks[j]);
-      if (j < NSLOT - 1) stage(a.v + step_off(t, j), Vs[j]);
+      stage_k(kbase + step_off(t, j), Ks(j));
+      if (j < NSLOT - 1) stage(a.v + step_off(t, j), Vs(j));
     }
   asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");
   f32x16 sc[KB / 32];
-  scores(Ks[0], sc);
+  scores(Ks(0), sc);
   hsap_lds_barrier();  // every wave has read K slot 0 before step 0 refills it
   const int32_t qstart = doc_window_start(a, docw, gq);
   const uint32_t span = (uint32_t)(gq - qstart);
@@ -673,7 +690,7 @@ __global__ __launch_bounds__(64 * WAVES, D == 64 ? 3 : 2) void attn_fwd_dl_kerne
   auto step = [&](int s, auto par, f32x16 (&sc)[KB / 32], f32x16 (&sn)[KB / 32]) __attribute__((always_inline)) {
     constexpr int PAR = decltype(par)::value;
     // the window of tile (s + NSLOT) / SUBS is needed now (rare vector load: every 64 tiles)
-    if (s + NSLOT < total && ((s + NSLOT) / SUBS) >> 6 > win_hi) load_window(win_hi + 1);
+    if (s + NSLOT < total && (at(s + NSLOT) / SUBS) >> 6 > win_hi) load_window(win_hi + 1);
     const uint32_t tile = tile_at(s);
     const float sl = FP8 ? fp8_step_scale(head_scale * kscale_s[chunk_of(tile)]) : head_scale;
     // s % NSLOT, (s + 1) % NSLOT and (s + NSLOT - 1) % NSLOT: this step's slot, the slot of the
@@ -682,8 +699,8 @@ __global__ __launch_bounds__(64 * WAVES, D == 64 ? 3 : 2) void attn_fwd_dl_kerne
     const int s1 = NSLOT == 2 ? PAR ^ 1 : (sk == NSLOT - 1 ? 0 : sk + 1);
     const int sv = NSLOT == 2 ? PAR ^ 1 : (sk == 0 ? NSLOT - 1 : sk - 1);
     const bool ldk = s + NSLOT < total, ldv = s + NSLOT - 1 < total;
-    if (ldk) stage_k(kbase + step_off(tile_at(s + NSLOT), s + NSLOT), Ks[s0]);
-    if (ldv) stage(a.v + step_off(tile_at(s + NSLOT - 1), s + NSLOT - 1), Vs[sv]);
+    if (ldk) stage_k(kbase + step_off(tile_at(s + NSLOT), s + NSLOT), Ks(s0));
+    if (ldv) stage(a.v + step_off(tile_at(s + NSLOT - 1), s + NSLOT - 1), Vs(sv));
 
     // Masked tile: a step whose keys no query of the wave may see is skipped (all its
     // probabilities would be 0: the running max, sum and O stay as they are), and one whose keys
@@ -738,11 +755,11 @@ __global__ __launch_bounds__(64 * WAVES, D == 64 ? 3 : 2) void attn_fwd_dl_kerne
           pb[nb][j >> 3][j & 7] = (__bf16)p;
         }
         if constexpr (FP8) {
-          if (nb == 0) scores(Ks[s1], sn);
+          if (nb == 0) scores(Ks(s1), sn);
         } else {
           bf16x8 kf[D / 16];
 #pragma unroll
-          for (int kk = 0; kk < D / 16; ++kk) kf[kk] = *(const bf16x8*)(Ks[s1] + 32 * nb * D + rowoff[kk]);
+          for (int kk = 0; kk < D / 16; ++kk) kf[kk] = *(const bf16x8*)(Ks(s1) + 32 * nb * D + rowoff[kk]);
           sn[nb] = f32x16{};
 #pragma unroll
           for (int kk = 0; kk < D / 16; ++kk) sn[nb] = mfma32(kf[kk], qf[kk], sn[nb]);
@@ -750,7 +767,7 @@ __global__ __launch_bounds__(64 * WAVES, D == 64 ? 3 : 2) void attn_fwd_dl_kerne
       }
       l_run += rs;
 
-      const __bf16* V = Vs[s0];
+      const __bf16* V = Vs(s0);
 #pragma unroll
       for (int nb = 0; nb < KB / 32; ++nb)
 #pragma unroll
@@ -765,7 +782,7 @@ __global__ __launch_bounds__(64 * WAVES, D == 64 ? 3 : 2) void attn_fwd_dl_kerne
       if constexpr (D == 128 && !FP8) block_order();
       __builtin_amdgcn_s_setprio(0);
     } else {
-      scores(Ks[s1], sn);
+      scores(Ks(s1), sn);
     }
     // K(s + 2) and V(s + 1) must have landed before the next step.  Three slots: they were
     // issued one step ago, and this step's own transfers (UK instructions for K, U for V) stay in
@@ -780,7 +797,19 @@ __global__ __launch_bounds__(64 * WAVES, D == 64 ? 3 : 2) void attn_fwd_dl_kerne
     }
     sk = s1;
   };
-  if constexpr (D == 64) {
+  if constexpr (KS > 1) {
+    // every stream takes part in the barriers of the longest one (the first)
+    const int most = (run_steps + KS - 1) / KS;
+    f32x16 sn[KB / 32];
+    for (int s = 0; s < most; s += 2) {
+      if (s < total) step(s, std::integral_constant<int, 0>{}, sc, D == 64 ? sc : sn);
+      else vm_wait_barrier<0>();
+      if (s + 1 < most) {
+        if (s + 1 < total) step(s + 1, std::integral_constant<int, 1>{}, D == 64 ? sc : sn, sc);
+        else vm_wait_barrier<0>();
+      }
+    }
+  } else if constexpr (D == 64) {
     // one score array: each 32-key half is replaced once its exponentials are formed (fewer registers,
     // more waves per SIMD)
     for (int s = 0; s < total; s += 2) {
@@ -792,6 +821,35 @@ __global__ __launch_bounds__(64 * WAVES, D == 64 ? 3 : 2) void attn_fwd_dl_kerne
     for (int s = 0; s < total; s += 2) {
       step(s, std::integral_constant<int, 0>{}, sc, sn);
       if (s + 1 < total) step(s + 1, std::integral_constant<int, 1>{}, sn, sc);
+    }
+  }
+
+  if constexpr (KS > 1) {
+    // The streams' running maxima, sums and O to LDS (register by register: consecutive lanes, no bank
+    // conflict; the loop ended with a barrier and no transfer is in flight), combined in stream order.
+    float* const res = (float*)rings;
+    if (ks > 0) {
+      float* const mine = res + ((ks - 1) * WAVES + w) * (D / 2 + 2) * 64 + lane;
+#pragma unroll
+      for (int mb = 0; mb < D / 32; ++mb)
+#pragma unroll
+        for (int j = 0; j < 16; ++j) mine[(16 * mb + j) * 64] = o[mb][j];
+      mine[(D / 2) * 64] = m_run;
+      mine[(D / 2 + 1) * 64] = l_run;
+    }
+    hsap_lds_barrier();
+    if (ks > 0) return;
+    for (int x = 1; x < KS; ++x) {
+      const float* const other = res + ((x - 1) * WAVES + w) * (D / 2 + 2) * 64 + lane;
+      const float m2 = other[(D / 2) * 64], l2 = other[(D / 2 + 1) * 64];
+      const float m = fmaxf(m_run, m2), m_use = m == NEG_INF ? 0.f : m;
+      const float f1 = fast_exp2(m_run - m_use), f2 = fast_exp2(m2 - m_use);
+      l_run = l_run * f1 + l2 * f2;
+      m_run = m;
+#pragma unroll
+      for (int mb = 0; mb < D / 32; ++mb)
+#pragma unroll
+        for (int j = 0; j < 16; ++j) o[mb][j] = o[mb][j] * f1 + other[(16 * mb + j) * 64] * f2;
     }
   }
 
@@ -823,24 +881,35 @@ __global__ __launch_bounds__(64 * WAVES, D == 64 ? 3 : 2) void attn_fwd_dl_kerne
   }
 }
 
-template <int D, int BN, int WAVES, bool FUSED, bool FP8 = false>
-static hsap_status launch_dl(const FwdArgs& a, int64_t num_runs, hipStream_t stream) {
+template <int D, int BN, int WAVES, bool FUSED, bool FP8, int KS>
+static hsap_status launch_dl_ks(const FwdArgs& a, int64_t num_runs, hipStream_t stream) {
   const int64_t blocks = num_runs * a.hq;
   if (blocks > INT32_MAX) HSAP_FAIL(HSAP_ERR_INVALID_ARG, "too many runs x heads");
   if constexpr (!FUSED && !FP8) {
     if (!a.runs) {
-      hipLaunchKernelGGL((attn_fwd_dl_kernel<D, BN, WAVES, false, false, true>), dim3((unsigned)blocks), dim3(64 * WAVES),
-                         0, stream, a);
+      hipLaunchKernelGGL((attn_fwd_dl_kernel<D, BN, WAVES, false, false, true, KS>), dim3((unsigned)blocks),
+                         dim3(64 * WAVES * KS), 0, stream, a);
       const hipError_t e = hipGetLastError();
       if (e != hipSuccess) HSAP_FAIL(HSAP_ERR_HIP, "attn_fwd launch: %s", hipGetErrorString(e));
       return HSAP_OK;
     }
   }
-  hipLaunchKernelGGL((attn_fwd_dl_kernel<D, BN, WAVES, FUSED, FP8>), dim3((unsigned)blocks), dim3(64 * WAVES), 0, stream,
-                     a);
+  hipLaunchKernelGGL((attn_fwd_dl_kernel<D, BN, WAVES, FUSED, FP8, false, KS>), dim3((unsigned)blocks),
+                     dim3(64 * WAVES * KS), 0, stream, a);
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) HSAP_FAIL(HSAP_ERR_HIP, "attn_fwd launch: %s", hipGetErrorString(e));
   return HSAP_OK;
+}
+
+template <int D, int BN, int WAVES, bool FUSED, bool FP8 = false>
+static hsap_status launch_dl(const FwdArgs& a, int64_t num_runs, hipStream_t stream) {
+  if constexpr (WAVES < 8 && !FP8) {
+    const int ks = key_streams(D, 32 * WAVES, a.geom.n / (32 * WAVES) * a.hq * (FUSED ? 1 : a.geom.P));
+    if constexpr (D == 64 && WAVES == 2)
+      if (ks == 4) return launch_dl_ks<D, BN, WAVES, FUSED, FP8, 4>(a, num_runs, stream);
+    if (ks >= 2) return launch_dl_ks<D, BN, WAVES, FUSED, FP8, 2>(a, num_runs, stream);
+  }
+  return launch_dl_ks<D, BN, WAVES, FUSED, FP8, 1>(a, num_runs, stream);
 }
 
 template <int D, int BN, int WAVES, bool FUSED, bool FP8 = false>
@@ -948,6 +1017,12 @@ static int blocks_per_cu(Kernel kernel, int threads) {
   return blocks;
 }
 
+int fwd_key_streams(const hsap_attn_desc* desc) {
+  Geom geom;
+  if (check_attn(desc, &geom) != HSAP_OK) return 1;
+  return key_streams(desc->head_dim, desc->shard.block_m, geom.n / desc->shard.block_m * desc->heads_q * geom.P);
+}
+
 int fwd_resident_per_cu(const hsap_attn_desc* desc) {
   Geom geom;
   if (check_attn(desc, &geom) != HSAP_OK) return 0;
@@ -957,10 +1032,15 @@ int fwd_resident_per_cu(const hsap_attn_desc* desc) {
   if (packed && d == 128 && bm == 256)
     return bn == 128 ? blocks_per_cu(attn_fwd_dl_kernel<128, 128, 8, false>, 512)
                      : blocks_per_cu(attn_fwd_dl_kernel<128, 64, 8, false>, 512);
-#define HSAP_OCC_CASE(D_, BN_, W_) \
-  if (d == D_ && bn == BN_ && bm == 32 * W_) \
-    return packed ? blocks_per_cu(attn_fwd_dl_kernel<D_, BN_, W_, false>, 64 * W_) \
-                  : blocks_per_cu(attn_fwd_kernel<D_, BN_, W_, false>, 64 * W_);
+  const int ks = packed ? fwd_key_streams(desc) : 1;
+  if (d == 64 && bm == 64 && ks == 4)
+    return bn == 128 ? blocks_per_cu(attn_fwd_dl_kernel<64, 128, 2, false, false, false, 4>, 512)
+                     : blocks_per_cu(attn_fwd_dl_kernel<64, 64, 2, false, false, false, 4>, 512);
+#define HSAP_OCC_CASE(D_, BN_, W_)                                                                              \
+  if (d == D_ && bn == BN_ && bm == 32 * W_)                                                                    \
+    return !packed   ? blocks_per_cu(attn_fwd_kernel<D_, BN_, W_, false>, 64 * W_)                              \
+           : ks == 2 ? blocks_per_cu(attn_fwd_dl_kernel<D_, BN_, W_, false, false, false, 2>, 128 * W_)         \
+                     : blocks_per_cu(attn_fwd_dl_kernel<D_, BN_, W_, false>, 64 * W_);
   HSAP_OCC_CASE(128, 128, 4)
   HSAP_OCC_CASE(128, 64, 4)
   HSAP_OCC_CASE(128, 128, 2)

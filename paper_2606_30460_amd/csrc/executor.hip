@@ -236,6 +236,21 @@ hsap_status hsap_executor_plan(hsap_executor* ex, const int32_t* cu_seqlens, int
   int32_t split = ex->max_run_tiles;
   if (split < 0) split = hsap_split_length(&sd, T, ex->desc.heads_q, ex->resident_workgroups);
   if (split < 0) return HSAP_ERR_INVALID_ARG;
+  // A workgroup with several key streams takes that many tiles of its run at a time: when no run is
+  // longer than the split times the streams, pieces would only add a merge (2048 tokens x 4 heads of 64:
+  // the 3.9 us merge of one q-tile).
+  if (ex->max_run_tiles < 0 && split > 0) {
+    const int streams = fwd_key_streams(&ex->desc);
+    if (streams > 1) {
+      int64_t longest = 0, len = 0;  // the tiles are in (ring step, q-tile, k-tile) order
+      for (int64_t i = 0; i < T; ++i) {
+        const hsap_tile &t = ex->tiles[(size_t)i], &u = ex->tiles[(size_t)std::max<int64_t>(i - 1, 0)];
+        len = i > 0 && t.chunk == u.chunk && t.q_tile == u.q_tile ? len + 1 : 1;
+        longest = std::max(longest, len);
+      }
+      if (longest <= (int64_t)split * streams) split = 0;
+    }
+  }
   int64_t RQ = 0;
   int32_t slots = 0;
   st = runs_for(ex, HSAP_MAJOR_Q, split, ex->sorted_q, ex->runs_q, &RQ, &slots);

@@ -70,6 +70,26 @@ hsap_status check_attn(const hsap_attn_desc* d, Geom* g);
 // must already pass check_attn.
 bool backward_supported(const hsap_attn_desc* d);
 
+// Key streams per workgroup of the forward and dQ kernels (their KS): the waves of a q-tile are
+// repeated KS times, each set takes every KS-th 64-key step of the run and the results are combined
+// in LDS at the end, so a run's chain of steps is KS times shorter at the same work.  That pays while
+// the grid leaves the chip idle.  The choice depends on the shape alone -- `items`, the (q-tile, head)
+// pairs of the call (times the chunks for the partial forward, whose runs are one per chunk) -- so that
+// calls over the same tiles give the same bits however their lists are cut.  Measured on one
+// document, forward / dQ in us, one stream -> KS:
+//   head_dim 64, 64-row q-tiles:  256 items of 16 tiles 29.5 / 34.0 -> 16.0 / 18.5 (four streams),
+//     512 items 30.7 / 35.8 -> 20.8 / 25.7 (two), 1024 items of 4 tiles 13.0 / 22.5 -> 16.2 / 23.3 (two)
+//   head_dim 64, 128-row:  256 items 31.9 / 35.4 -> 25.0 / 28.7, 512 items of 5 tiles 13.9 / 20.9 -> 16.7 / 22.8
+//   head_dim 128, 128-row: 128 items 36.6 / 55.0 -> 32.1 / 45.7, 256 items of 2.5 tiles 15.7 / 23.5 -> 15.7 / 23.8,
+//     512 items 23.0 / 31.7 -> 29.5 / 42.2
+//   head_dim 128, 64-row:  256 items 41.8 / 53.1 -> 29.7 / 36.0, 512 items of 2.5 tiles 17.0 / 23.1 -> 19.8 / 25.6
+constexpr int64_t kComputeUnits = 256;
+inline int key_streams(int head_dim, int block_m, int64_t items) {
+  if (block_m > 128) return 1;
+  if (head_dim == 64 && block_m == 64) return items <= kComputeUnits ? 4 : items <= 2 * kComputeUnits ? 2 : 1;
+  return items <= (head_dim == 128 && block_m == 128 ? 3 * kComputeUnits / 4 : kComputeUnits) ? 2 : 1;
+}
+
 #if defined(__HIPCC__)
 // First index i of tiles[0 .. num - 1] (sorted by q_tile) with tiles[i].q_tile >= key, for the
 // tile-list entry points (one chunk's tiles in the planner's order).  Wave-wide: each round
@@ -120,6 +140,9 @@ __device__ inline hsap_run q_tile_run(const hsap_tile* tiles, int32_t num, int32
   const int32_t end = lower_bound_q_tile(tiles, num, qt + 1, lane);
   return hsap_run{0, qt, first, end - first};
 }
+
+// Key streams of the partial forward for the descriptor's shape.
+int fwd_key_streams(const hsap_attn_desc* d);
 
 // Workgroups of the bf16 partial forward resident on one compute unit for the descriptor's shape
 // (the runtime's occupancy of the kernel that runs); 0 when there is none.

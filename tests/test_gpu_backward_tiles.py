@@ -20,6 +20,11 @@ CASES = [
     (2048, 18, 9, 64, 128, 64, [41]),
     (256, 3, 1, 128, 64, 128, [64]),        # runs of one 64-row q-tile per head: two sub-tiles, four streams
     (128, 1, 1, 64, 64, 64, [128]),
+    # the dQ kernel's key streams: four at 256 q-tiles x heads (above), two at 288, 96 and 192, one at 208
+    (2048, 9, 9, 64, 64, 64, [700, 9]),
+    (2048, 6, 6, 64, 128, 64, [2048]),
+    (2048, 12, 4, 128, 128, 128, [5, 1200]),
+    (2048, 13, 13, 128, 128, 64, [5, 1200]),
 ]
 
 

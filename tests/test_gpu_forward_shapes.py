@@ -17,6 +17,15 @@ CASES = [
     (4096, 2, "zigzag", 0, 6, 3, 64, 64, 128, [1, 130, 7]),
     (64, 1, "contiguous", 0, 1, 1, 64, 64, 64, [1, 62]),        # one tile, one step
     (128, 2, "contiguous", 1, 1, 1, 128, 64, 64, [128]),
+    # q-tiles x heads on either side of where the key streams per workgroup change: four, two, one
+    (2048, 1, "contiguous", 0, 8, 8, 64, 64, 64, [900, 3, 70]),     # 256
+    (2048, 1, "contiguous", 0, 9, 3, 64, 64, 128, [900, 3, 70]),    # 288
+    (2048, 1, "contiguous", 0, 17, 17, 64, 64, 64, [900, 3, 70]),   # 544
+    (2048, 1, "contiguous", 0, 16, 8, 64, 128, 64, [2048]),         # 256: two, and 272: one
+    (2048, 1, "contiguous", 0, 17, 17, 64, 128, 128, [2048]),
+    (2048, 1, "contiguous", 0, 12, 4, 128, 128, 128, [5, 1200]),    # 192: two, and 208: one
+    (2048, 1, "contiguous", 0, 13, 13, 128, 128, 64, [5, 1200]),
+    (4096, 2, "zigzag", 1, 4, 4, 128, 64, 64, [4096]),              # 128 x 2 chunks
 ]
 
 
