@@ -736,9 +736,9 @@ typedef struct {
  *   options        HSAP_EXEC_* bits.
  *   max_run_tiles  q-major split: -1 picks hsap_split_length per plan from
  *                  hsap_fwd_resident_workgroups of the device current at
- *                  creation (no split when the kernel for a small shape reads several tiles of
- *                  a run at a time and the longest run is short enough for it), 0 never
- *                  splits, > 0 is used as given.  A plan whose split would need more than
+ *                  creation, but none (hsap_exec_info.split_length 0) unless the plan's
+ *                  longest run exceeds four times the average work per resident
+ *                  workgroup, 0 never splits, > 0 is used as given.  A plan whose split would need more than
  *                  HSAP_MAX_MERGE_PARTS partials is planned without split.
  *   out            receives the executor; NULL on failure.
  * Returns HSAP_ERR_HIP when device or pinned memory cannot be allocated.

@@ -60,7 +60,7 @@ struct hsap_executor {
 
   // device side
   DevBuf lists;  // [sorted_q | runs_q | sorted_k | runs_k | sorted_all | runs_all | cu | merged_tiles | zero_ktiles]
-  int32_t* doc_start = nullptr;  // start(t) per position, for the backward only
+  int32_t* doc_start = nullptr;  // start(t) at the shard's positions, from the backward's dQ kernel to its dK/dV kernel
   DevBuf o_part, lse_part;
   float* delta = nullptr;
 
@@ -75,7 +75,7 @@ struct hsap_executor {
   const hsap_run* d_runs_all = nullptr;
   const int32_t* d_merged_tiles = nullptr;
   const int32_t* d_zero_ktiles = nullptr;
-  const int32_t* d_cu = nullptr;  // the plan's cu_seqlens (the forwards search it for document starts)
+  const int32_t* d_cu = nullptr;  // the plan's cu_seqlens (searched for document starts)
   int32_t num_docs = 0;
   std::vector<uint8_t> chunk_has_tiles;
 };
@@ -236,20 +236,20 @@ hsap_status hsap_executor_plan(hsap_executor* ex, const int32_t* cu_seqlens, int
   int32_t split = ex->max_run_tiles;
   if (split < 0) split = hsap_split_length(&sd, T, ex->desc.heads_q, ex->resident_workgroups);
   if (split < 0) return HSAP_ERR_INVALID_ARG;
-  // A workgroup with several key streams takes that many tiles of its run at a time: when no run is
-  // longer than the split times the streams, pieces would only add a merge (2048 tokens x 4 heads of 64:
-  // the 3.9 us merge of one q-tile).
+  // The planner's split balances runs whose length could exceed the average work of a resident workgroup;
+  // pieces cost a prologue each, fp32 partials and the merge, so a split has to shorten the longest
+  // run there is by much: it is left out unless that run holds more than four times the average.
+  // Forward + merge with and without it: 32768 tokens, runs of up to 11 tiles for an average of 5.4: 48.1 and
+  // 38.8 us; 32 tiles for 14.2: 50.9 and 44.4 us; 8 tiles for 0.1 (one head): 18.2 and 20.2 us; 9 tiles for 2.3
+  // (2048 tokens x 4 heads of 64, one chunk): 12.6 and 9.8 us.
   if (ex->max_run_tiles < 0 && split > 0) {
-    const int streams = fwd_key_streams(&ex->desc);
-    if (streams > 1) {
-      int64_t longest = 0, len = 0;  // the tiles are in (ring step, q-tile, k-tile) order
-      for (int64_t i = 0; i < T; ++i) {
-        const hsap_tile &t = ex->tiles[(size_t)i], &u = ex->tiles[(size_t)std::max<int64_t>(i - 1, 0)];
-        len = i > 0 && t.chunk == u.chunk && t.q_tile == u.q_tile ? len + 1 : 1;
-        longest = std::max(longest, len);
-      }
-      if (longest <= (int64_t)split * streams) split = 0;
+    int64_t longest = 0, len = 0;  // the tiles are in (ring step, q-tile, k-tile) order
+    for (int64_t i = 0; i < T; ++i) {
+      const hsap_tile &t = ex->tiles[(size_t)i], &u = ex->tiles[(size_t)std::max<int64_t>(i - 1, 0)];
+      len = i > 0 && t.chunk == u.chunk && t.q_tile == u.q_tile ? len + 1 : 1;
+      longest = std::max(longest, len);
     }
+    if (longest * ex->resident_workgroups <= 4 * T * ex->desc.heads_q) split = 0;
   }
   int64_t RQ = 0;
   int32_t slots = 0;
@@ -332,8 +332,8 @@ hsap_status hsap_executor_plan(hsap_executor* ex, const int32_t* cu_seqlens, int
           if (!reached[(size_t)(c * nk + t)]) ex->zero_ktiles.push_back((int32_t)(c * nk + t));
   }
 
-  // 4. partial workspace for this plan's parts
-  const size_t part_rows = (size_t)ex->geom.n * ex->desc.heads_q;
+  // 4. partial workspace for this plan's parts (none when every q-tile is written final)
+  const size_t part_rows = ex->merged_tiles.empty() ? 0 : (size_t)ex->geom.n * ex->desc.heads_q;
   st = grow_device(ex->o_part, (size_t)parts * part_rows * ex->desc.head_dim * sizeof(float), stream);
   if (st == HSAP_OK) st = grow_device(ex->lse_part, (size_t)parts * part_rows * sizeof(float), stream);
   if (st != HSAP_OK) return st;
@@ -415,9 +415,14 @@ hsap_status hsap_executor_partial_forward(hsap_executor* ex, const void* q, cons
   if (!ex) HSAP_FAIL(HSAP_ERR_INVALID_ARG, "NULL executor");
   if (!ex->planned) HSAP_FAIL(HSAP_ERR_INVALID_ARG, "executor has no plan");
   if (!q || !k || !v || !o_out || !lse_out) HSAP_FAIL(HSAP_ERR_INVALID_ARG, "NULL pointer argument");
+  // a plan whose runs are all final has no partials (their buffers may not exist): the list buffer's
+  // address stands in for them, untouched
+  const bool partials = !ex->merged_tiles.empty();
+  float* const o_part = (float*)(partials ? ex->o_part.p : ex->lists.p);
+  float* const lse_part = (float*)(partials ? ex->lse_part.p : ex->lists.p);
   return executor_forward(&ex->desc, false, q, k, v, ex->d_cu, ex->num_docs, ex->d_tiles_q, ex->d_runs_q,
-                          ex->info.num_runs_q, (float*)ex->o_part.p, (float*)ex->lse_part.p, ex->info.num_parts,
-                          o_out, lse_out, (hipStream_t)hip_stream);
+                          ex->info.num_runs_q, o_part, lse_part, ex->info.num_parts, o_out, lse_out,
+                          (hipStream_t)hip_stream);
 }
 
 hsap_status hsap_executor_merge(hsap_executor* ex, void* o_out, float* lse_out, void* hip_stream) {

@@ -42,7 +42,9 @@ class ShardAttention:
 
     ``max_run_tiles``: longest q-major run before it is split into pieces
     (split-K over partial slots); None picks it from the plan and the number
-    of resident workgroups (hsap_split_length), 0 disables splitting.
+    of resident workgroups (hsap_split_length, and no split unless the longest
+    run exceeds four times the average per workgroup, as the executor
+    decides), 0 disables splitting.
     """
 
     def __init__(self, cu_seqlens, total_tokens: int, sp_degree: int, layout, shard_id: int, heads_q: int,
@@ -60,10 +62,17 @@ class ShardAttention:
         self.max_run_tiles = max_run_tiles
         self.planned = False
 
-    def _split(self, num_tiles: int) -> int:
+    def _split(self, tiles: np.ndarray) -> int:
         if self.max_run_tiles is not None:
             return int(self.max_run_tiles)
-        return L.split_length(self.shard, num_tiles, self.hq, _resident_workgroups(self.device, self.desc))
+        resident = _resident_workgroups(self.device, self.desc)
+        split = L.split_length(self.shard, len(tiles), self.hq, resident)
+        if split > 0:  # as the executor decides: no split unless the longest run is well above the average
+            runs = tiles[:, 0].astype(np.int64) << 32 | tiles[:, 1]
+            longest = int(np.unique(runs, return_counts=True)[1].max())
+            if longest * resident <= 4 * len(tiles) * self.hq:
+                split = 0
+        return split
 
     # ------------------------------------------------------------------ plan
     def plan(self, backward: bool = False) -> Dict:
@@ -73,7 +82,7 @@ class ShardAttention:
         self.step_offsets = p["step_offsets"]
         self.useful_pairs = p["useful_pairs"]
         self.chunks = [(self.shard.shard_id - s) % self.P for s in range(self.P)]
-        self.split = self._split(len(self.tiles))
+        self.split = self._split(self.tiles)
         tiles_q, runs_q, self.num_slots = L.plan_runs(self.shard, self.tiles, L.MAJOR_Q, self.split)
         self.runs_q_host = runs_q
         self.present = sorted(set(runs_q[:, 0].tolist()))
