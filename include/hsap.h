@@ -692,10 +692,11 @@ hsap_status hsap_convert_f32_bf16(const float* src, void* dst, int64_t count, vo
  * An executor owns: a ring of 16 pinned staging buffers for the planner's lists, one
  * device list buffer, the fp32 partial outputs of the forward (grown to the
  * largest plan seen) and, with HSAP_EXEC_BACKWARD, the device doc_start
- * array and the backward's delta.  The forwards take document starts from
+ * array and the backward's delta.  The kernels take document starts from
  * the uploaded cu_seqlens: each wave finds the document of its first query
- * by binary search and scans the boundaries among its 32 queries, so a
- * forward-only step runs no hsap_doc_start.  Buffers grow on demand; a
+ * by a search and scans the boundaries among its 32 queries, so no step
+ * runs hsap_doc_start (the dQ kernel leaves the starts of the shard's rows in
+ * the doc_start array for the dK/dV kernel).  Buffers grow on demand; a
  * growth synchronises the stream first.
  *
  * Threading and streams: one executor is used by one host thread at a time,
@@ -755,8 +756,7 @@ void hsap_executor_destroy(hsap_executor* ex);
  * the q-major runs (partial slots renumbered densely 0..num_parts-1 in
  * increasing original slot order) and, per the options, the k-major and
  * MAJOR_Q_ALL runs; then one asynchronous upload of every list and
- * cu_seqlens from a pinned staging buffer, and (HSAP_EXEC_BACKWARD only)
- * hsap_doc_start, on `stream`.
+ * cu_seqlens from a pinned staging buffer on `stream`.
  * The host blocks only when the staging buffer it is about to reuse may not
  * have been uploaded yet: it waits for an event recorded after every 8th
  * upload (events cost the stream a gap each), at most 16 plans in flight.
@@ -803,8 +803,8 @@ hsap_status hsap_executor_merge(hsap_executor* ex, void* o_out, float* lse_out, 
  * them), then the kernels of hsap_attn_bwd_bf16 over the k-major and
  * MAJOR_Q_ALL runs, which write every other row of those chunks.  The dQ
  * kernel runs first and computes the preprocess (delta of
- * hsap_attn_bwd_preprocess) for its rows from o and d_o; the dK/dV kernel
- * reads it.
+ * hsap_attn_bwd_preprocess) for its rows from o and d_o, and their document
+ * starts from cu_seqlens; the dK/dV kernel reads both.
  *   q, k, v  as for the forward;  d_o, o  device bf16 [n, Hq, d] (o: the
  *            forward's output);  lse  device fp32 [Hq, n] (the forward's).
  *   dq       device bf16 [n, Hq, d].

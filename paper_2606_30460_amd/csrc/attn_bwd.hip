@@ -42,6 +42,9 @@ struct BwdArgs {
   const __bf16* o;     // when set, the dQ kernel computes delta from O and dO itself, writing delta_out
   float* delta_out;
   const int32_t* doc_start;
+  const int32_t* cu;      // when set, the dQ kernel finds document starts here, writing them to start_out
+  int32_t num_docs;
+  int32_t* start_out;
   const hsap_tile* tiles;
   const hsap_run* runs;
   float* dq;       // fp32 accumulators (+=), or
@@ -632,8 +635,7 @@ __global__ __launch_bounds__(64 * WAVES * KS, 2) void attn_bwd_dq_kernel(BwdArgs
     return;
   }
   const int32_t gq = (int32_t)global_pos(a.geom, a.shard, qrow);
-  const int32_t qstart = a.doc_start[gq];
-  const uint32_t span = (uint32_t)(gq - qstart);
+  const DocWindow docw = doc_window(a.doc_start, a.cu, a.num_docs, gq, lane);
   const float lse_raw = a.lse[(int64_t)h * n + qrow];
   const float lse2 = lse_raw == NEG_INF ? __builtin_inff() : lse_raw * LOG2E;  // no key: P = 0
   bf16x8 qf[D / 16], of[D / 16];
@@ -748,6 +750,9 @@ __global__ __launch_bounds__(64 * WAVES * KS, 2) void attn_bwd_dq_kernel(BwdArgs
   // counter also counts the step's transfers, each step would wait for the next step's K and V.
 #pragma unroll
   for (int kk = 0; kk < D / 16; ++kk) asm volatile("" ::"v"(qf[kk]), "v"(of[kk]));
+  const int32_t qstart = doc_window_start(a.cu, a.num_docs, docw, gq);
+  const uint32_t span = (uint32_t)(gq - qstart);
+  if (a.start_out && h == 0 && hi == 0 && ks == 0) a.start_out[gq] = qstart;  // read by the dK/dV kernel, launched after
   asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");
 
   // one 64-key step from slot PAR (= s % 2, a compile-time constant, so every slot address is an
@@ -911,7 +916,7 @@ static hsap_status launch_dq_ks(const BwdArgs& a, int64_t num_runs, hipStream_t 
 template <int D, int BN, int WAVES, bool BF16OUT, bool LIST = false>
 static hsap_status launch_dq(const BwdArgs& a, int64_t num_runs, hipStream_t stream) {
   if constexpr (WAVES < 8) {
-    const int ks = key_streams(D, 32 * WAVES, a.geom.n / (32 * WAVES) * a.hq);
+    const int ks = key_streams(D, 32 * WAVES, a.geom.n / (32 * WAVES) * a.hq, LIST ? a.geom.ns : a.geom.Ns);
     if constexpr (D == 64 && WAVES == 2)
       if (ks == 4) return launch_dq_ks<D, BN, WAVES, BF16OUT, LIST, 4>(a, num_runs, stream);
     if (ks >= 2) return launch_dq_ks<D, BN, WAVES, BF16OUT, LIST, 2>(a, num_runs, stream);
@@ -938,11 +943,12 @@ namespace hsap {
 
 // shared checks and dispatch of the fp32-accumulating and the bf16-storing backward
 template <bool BF16OUT>
-// o == NULL: delta is an input.  Otherwise the dQ kernel computes delta from o and d_o into
-// delta_out, and the dK/dV kernel (launched after it) reads it there.
+// o == NULL: delta and doc_start are inputs.  Otherwise the dQ kernel computes delta from o and d_o into
+// delta_out and the rows' document starts from cu into doc_start (as the forwards find them), and the
+// dK/dV kernel (launched after it) reads both there.
 static hsap_status backward(const hsap_attn_desc* desc, const void* q, const void* k, const void* v, const void* d_o,
                             const void* o, const float* lse, const float* delta, float* delta_out,
-                            const int32_t* doc_start, const hsap_tile* tiles_k, const hsap_run* runs_k,
+                            const int32_t* cu, int32_t num_docs, const int32_t* doc_start, const hsap_tile* tiles_k, const hsap_run* runs_k,
                             int64_t num_runs_k, const hsap_tile* tiles_q, const hsap_run* runs_q,
                             int64_t num_runs_q, void* dq, void* dk, void* dv, hipStream_t s) {
   Geom geom;
@@ -977,6 +983,11 @@ static hsap_status backward(const hsap_attn_desc* desc, const void* q, const voi
   a.o = (const __bf16*)o;
   a.delta_out = delta_out;
   a.doc_start = doc_start;
+  if (o) {
+    a.cu = cu;
+    a.num_docs = num_docs;
+    a.start_out = const_cast<int32_t*>(doc_start);
+  }
   if (BF16OUT) {
     a.dq16 = (__bf16*)dq;
     a.dk16 = (__bf16*)dk;
@@ -1112,7 +1123,7 @@ extern "C" hsap_status hsap_partial_attn_bwd_runs(const hsap_attn_desc* desc, co
                                              const hsap_run* runs_q, int64_t num_runs_q, float* dq_acc,
                                              float* dk_acc, float* dv_acc, void* hip_stream) {
   clear_error();
-  return backward<false>(desc, q, k, v, d_o, nullptr, lse, delta, nullptr, doc_start, tiles_k, runs_k, num_runs_k,
+  return backward<false>(desc, q, k, v, d_o, nullptr, lse, delta, nullptr, nullptr, 0, doc_start, tiles_k, runs_k, num_runs_k,
                          tiles_q, runs_q, num_runs_q, dq_acc, dk_acc, dv_acc, (hipStream_t)hip_stream);
 }
 
@@ -1122,18 +1133,19 @@ extern "C" hsap_status hsap_attn_bwd_bf16(const hsap_attn_desc* desc, const void
                                           int64_t num_runs_k, const hsap_tile* tiles_q, const hsap_run* runs_q,
                                           int64_t num_runs_q, void* dq, void* dk, void* dv, void* hip_stream) {
   clear_error();
-  return backward<true>(desc, q, k, v, d_o, nullptr, lse, delta, nullptr, doc_start, tiles_k, runs_k, num_runs_k,
+  return backward<true>(desc, q, k, v, d_o, nullptr, lse, delta, nullptr, nullptr, 0, doc_start, tiles_k, runs_k, num_runs_k,
                         tiles_q, runs_q, num_runs_q, dq, dk, dv, (hipStream_t)hip_stream);
 }
 
 namespace hsap {
 hsap_status attn_bwd_bf16_delta(const hsap_attn_desc* desc, const void* q, const void* k, const void* v,
                                 const void* d_o, const void* o, const float* lse, float* delta,
-                                const int32_t* doc_start, const hsap_tile* tiles_k, const hsap_run* runs_k,
-                                int64_t num_runs_k, const hsap_tile* tiles_q, const hsap_run* runs_q,
-                                int64_t num_runs_q, void* dq, void* dk, void* dv, hipStream_t stream) {
-  if (!o) HSAP_FAIL(HSAP_ERR_INVALID_ARG, "NULL o");
-  return backward<true>(desc, q, k, v, d_o, o, lse, nullptr, delta, doc_start, tiles_k, runs_k, num_runs_k, tiles_q,
-                        runs_q, num_runs_q, dq, dk, dv, stream);
+                                const int32_t* cu_seqlens, int32_t num_docs, int32_t* doc_start,
+                                const hsap_tile* tiles_k, const hsap_run* runs_k, int64_t num_runs_k,
+                                const hsap_tile* tiles_q, const hsap_run* runs_q, int64_t num_runs_q, void* dq,
+                                void* dk, void* dv, hipStream_t stream) {
+  if (!o || !cu_seqlens || num_docs < 1) HSAP_FAIL(HSAP_ERR_INVALID_ARG, "NULL o or no cumulative lengths");
+  return backward<true>(desc, q, k, v, d_o, o, lse, nullptr, delta, cu_seqlens, num_docs, doc_start, tiles_k, runs_k,
+                        num_runs_k, tiles_q, runs_q, num_runs_q, dq, dk, dv, stream);
 }
 }  // namespace hsap

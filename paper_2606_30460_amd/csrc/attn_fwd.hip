@@ -66,61 +66,6 @@ struct FwdArgs {
   float scale_log2;
 };
 
-// Document start of this lane's query (global position gq), in two parts so the memory access
-// is issued at kernel start and consumed after the prologue.  With per-position starts it is one
-// load.  From the cumulative lengths instead: a wave's 32 queries (lanes 0..31; lane l ^ 32 holds
-// the query of lane l) are 32 consecutive positions -- every piece of a shard is a multiple of
-// the 64-, 128- or 256-row q-tile -- so at most 31 document boundaries lie after the document of
-// lane 0's position g_lo, up to lane 31's position g_hi.  The wave loads 64 consecutive entries
-// of cu_seqlens, starting at most 31 entries before the document of g_lo (a 64-way search in
-// rounds narrows the start when there are more than 32 entries), and each lane takes the largest
-// entry not above its position with ballots and lane reads: no further memory access.
-struct DocWindow {
-  int32_t w;           // cu[base + lane], or this lane's start when per-position starts are given
-  int32_t g_lo, g_hi;  // positions of the wave's first and last query
-};
-
-__device__ __forceinline__ DocWindow doc_window(const FwdArgs& a, int32_t gq, int lane) {
-  DocWindow r{};
-  if (!a.cu) {
-    r.w = a.doc_start[gq];
-    return r;
-  }
-  r.g_lo = __builtin_amdgcn_readlane(gq, 0);
-  r.g_hi = __builtin_amdgcn_readlane(gq, 31);
-  const int32_t nd = a.num_docs;
-  int32_t base = 0, len = nd + 1;  // the document of g_lo is one of base .. base + len - 1
-  while (len > 32) {
-    const int32_t stride = (len + 63) >> 6;
-    const int32_t v = a.cu[min(base + lane * stride, nd)];
-    base += stride * (__popcll(__builtin_amdgcn_ballot_w64(v <= r.g_lo)) - 1);
-    len = stride;
-  }
-  r.w = a.cu[min(base + lane, nd)];
-  return r;
-}
-
-__device__ __forceinline__ int32_t doc_window_start(const FwdArgs& a, const DocWindow& r, int32_t gq) {
-  if (!a.cu) return r.w;
-  const int32_t lo = __popcll(__builtin_amdgcn_ballot_w64(r.w <= r.g_lo)) - 1;    // document of g_lo
-  const int32_t last = __popcll(__builtin_amdgcn_ballot_w64(r.w <= r.g_hi)) - 1;  // last boundary <= g_hi
-  int32_t start = __builtin_amdgcn_readlane(r.w, lo);
-  if (last >= 63) {  // more boundaries than the window holds (not reachable with validated shapes)
-    int32_t l = 0, h = a.num_docs;
-    while (h - l > 1) {
-      const int32_t mid = (l + h) >> 1;
-      if (a.cu[mid] <= gq) l = mid;
-      else h = mid;
-    }
-    return a.cu[l];
-  }
-  for (int32_t j = lo + 1; j <= last; ++j) {
-    const int32_t b = __builtin_amdgcn_readlane(r.w, j);
-    if (gq >= b) start = b;
-  }
-  return start;
-}
-
 // fp8 scores: the exp2 scale of a step, q_scale[h] * k_scale[chunk, g] * scale * log2(e), kept at
 // or above the smallest normal float.  A scale is 0 only when its slice is all zeros, so every
 // code and every finite score of the step is 0 and stays 0 after the multiply, while a masked
@@ -179,7 +124,7 @@ __global__ __launch_bounds__(64 * WAVES, 2) void attn_fwd_kernel(FwdArgs a) {
   }
 
   const int32_t gq = (int32_t)global_pos(a.geom, a.shard, qrow);
-  const DocWindow docw = doc_window(a, gq, lane);
+  const DocWindow docw = doc_window(a.doc_start, a.cu, a.num_docs, gq, lane);
   bf16x8 qf[D / 16];
   i32x8 qf8[2];  // fp8: lane half hi holds bytes 64 kk + 32 hi .. +31 of its query's row
   if constexpr (FP8) {
@@ -303,7 +248,7 @@ __global__ __launch_bounds__(64 * WAVES, 2) void attn_fwd_kernel(FwdArgs a) {
   f32x16 sc[KB / 32];
   scores(0, sc);
   __syncthreads();  // every wave has read K slot 0 before iteration 0 refills it
-  const int32_t qstart = doc_window_start(a, docw, gq);  // first needed by the masks of step 0
+  const int32_t qstart = doc_window_start(a.cu, a.num_docs, docw, gq);  // first needed by the masks of step 0
   const uint32_t span = (uint32_t)(gq - qstart);  // key j is allowed iff 0 <= j - start <= span
 
   // one 64-key step: softmax and PV of step s from `sc`, scores of step s + 1 into `sn`; the
@@ -513,7 +458,7 @@ __global__ __launch_bounds__(64 * WAVES * KS, D == 64 && KS == 1 ? 3 : 2) void a
   }
 
   const int32_t gq = (int32_t)global_pos(a.geom, a.shard, qrow);
-  const DocWindow docw = doc_window(a, gq, lane);
+  const DocWindow docw = doc_window(a.doc_start, a.cu, a.num_docs, gq, lane);
   bf16x8 qf[D / 16];
   i32x8 qf8[2];  // fp8: lane half hi holds bytes 64 kk + 32 hi .. +31 of its query's row
   if constexpr (FP8) {
@@ -661,7 +606,7 @@ __global__ __launch_bounds__(64 * WAVES * KS, D == 64 && KS == 1 ? 3 : 2) void a
   f32x16 sc[KB / 32];
   scores(Ks(0), sc);
   hsap_lds_barrier();  // every wave has read K slot 0 before step 0 refills it
-  const int32_t qstart = doc_window_start(a, docw, gq);
+  const int32_t qstart = doc_window_start(a.cu, a.num_docs, docw, gq);
   const uint32_t span = (uint32_t)(gq - qstart);
 
   int sk = 0;  // s % NSLOT
@@ -904,7 +849,8 @@ static hsap_status launch_dl_ks(const FwdArgs& a, int64_t num_runs, hipStream_t 
 template <int D, int BN, int WAVES, bool FUSED, bool FP8 = false>
 static hsap_status launch_dl(const FwdArgs& a, int64_t num_runs, hipStream_t stream) {
   if constexpr (WAVES < 8 && !FP8) {
-    const int ks = key_streams(D, 32 * WAVES, a.geom.n / (32 * WAVES) * a.hq * (FUSED ? 1 : a.geom.P));
+    const int ks = FUSED ? key_streams(D, 32 * WAVES, a.geom.n / (32 * WAVES) * a.hq, a.geom.Ns)
+                         : fwd_key_streams(D, 32 * WAVES, a.hq, a.geom);
     if constexpr (D == 64 && WAVES == 2)
       if (ks == 4) return launch_dl_ks<D, BN, WAVES, FUSED, FP8, 4>(a, num_runs, stream);
     if (ks >= 2) return launch_dl_ks<D, BN, WAVES, FUSED, FP8, 2>(a, num_runs, stream);
@@ -1017,12 +963,6 @@ static int blocks_per_cu(Kernel kernel, int threads) {
   return blocks;
 }
 
-int fwd_key_streams(const hsap_attn_desc* desc) {
-  Geom geom;
-  if (check_attn(desc, &geom) != HSAP_OK) return 1;
-  return key_streams(desc->head_dim, desc->shard.block_m, geom.n / desc->shard.block_m * desc->heads_q * geom.P);
-}
-
 int fwd_resident_per_cu(const hsap_attn_desc* desc) {
   Geom geom;
   if (check_attn(desc, &geom) != HSAP_OK) return 0;
@@ -1032,7 +972,7 @@ int fwd_resident_per_cu(const hsap_attn_desc* desc) {
   if (packed && d == 128 && bm == 256)
     return bn == 128 ? blocks_per_cu(attn_fwd_dl_kernel<128, 128, 8, false>, 512)
                      : blocks_per_cu(attn_fwd_dl_kernel<128, 64, 8, false>, 512);
-  const int ks = packed ? fwd_key_streams(desc) : 1;
+  const int ks = packed ? fwd_key_streams(d, bm, desc->heads_q, geom) : 1;
   if (d == 64 && bm == 64 && ks == 4)
     return bn == 128 ? blocks_per_cu(attn_fwd_dl_kernel<64, 128, 2, false, false, false, 4>, 512)
                      : blocks_per_cu(attn_fwd_dl_kernel<64, 64, 2, false, false, false, 4>, 512);

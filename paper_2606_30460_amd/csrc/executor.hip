@@ -392,11 +392,6 @@ hsap_status hsap_executor_plan(hsap_executor* ex, const int32_t* cu_seqlens, int
   ex->d_cu = d + o_cu;
   ex->num_docs = num_docs;
 
-  // 6. start(t) for every position, read by the backward's masks (the forwards search cu_seqlens)
-  if (ex->options & HSAP_EXEC_BACKWARD) {
-    st = hsap_doc_start(d + o_cu, num_docs, ex->geom.N, ex->doc_start, hip_stream);
-    if (st != HSAP_OK) return st;
-  }
   ex->planned = true;
   return HSAP_OK;
 }
@@ -476,9 +471,9 @@ hsap_status hsap_executor_backward(hsap_executor* ex, const void* q, const void*
   hsap_status st = zero_tiles(dk, dv, ex->d_zero_ktiles, (int32_t)ex->zero_ktiles.size(), ktile_bytes, stream);
   // the preprocess (delta = rowsum(dO o O)) runs inside the dQ kernel, which reads dO anyway
   if (st == HSAP_OK)
-    st = attn_bwd_bf16_delta(&ex->desc, q, k, v, d_o, o, lse, ex->delta, ex->doc_start, ex->d_tiles_k, ex->d_runs_k,
-                             ex->info.num_runs_k, ex->d_tiles_all, ex->d_runs_all, ex->info.num_runs_all, dq, dk, dv,
-                             stream);
+    st = attn_bwd_bf16_delta(&ex->desc, q, k, v, d_o, o, lse, ex->delta, ex->d_cu, ex->num_docs, ex->doc_start,
+                             ex->d_tiles_k, ex->d_runs_k, ex->info.num_runs_k, ex->d_tiles_all, ex->d_runs_all,
+                             ex->info.num_runs_all, dq, dk, dv, stream);
   return st;
 }
 

@@ -76,7 +76,8 @@ bool backward_supported(const hsap_attn_desc* d);
 // the grid leaves the chip idle.  The choice depends on the shape alone -- `items`, the (q-tile, head)
 // pairs of the call (times the chunks for the partial forward, whose runs are one per chunk) -- so that
 // calls over the same tiles give the same bits however their lists are cut.  Measured on one
-// document, forward / dQ in us, one stream -> KS:
+// document, forward / dQ in us, one stream -> KS (runs of at most 8 steps gain nothing: 13.9 / 20.0 ->
+// 13.8 / 19.2 at 512 keys, and a step of 128-key chunks lost 1.5 %; `keys` is the most a run can have):
 //   head_dim 64, 64-row q-tiles:  256 items of 16 tiles 29.5 / 34.0 -> 16.0 / 18.5 (four streams),
 //     512 items 30.7 / 35.8 -> 20.8 / 25.7 (two), 1024 items of 4 tiles 13.0 / 22.5 -> 16.2 / 23.3 (two)
 //   head_dim 64, 128-row:  256 items 31.9 / 35.4 -> 25.0 / 28.7, 512 items of 5 tiles 13.9 / 20.9 -> 16.7 / 22.8
@@ -84,10 +85,15 @@ bool backward_supported(const hsap_attn_desc* d);
 //     512 items 23.0 / 31.7 -> 29.5 / 42.2
 //   head_dim 128, 64-row:  256 items 41.8 / 53.1 -> 29.7 / 36.0, 512 items of 2.5 tiles 17.0 / 23.1 -> 19.8 / 25.6
 constexpr int64_t kComputeUnits = 256;
-inline int key_streams(int head_dim, int block_m, int64_t items) {
-  if (block_m > 128) return 1;
+inline int key_streams(int head_dim, int block_m, int64_t items, int64_t keys) {
+  if (block_m > 128 || keys < 1024) return 1;
   if (head_dim == 64 && block_m == 64) return items <= kComputeUnits ? 4 : items <= 2 * kComputeUnits ? 2 : 1;
   return items <= (head_dim == 128 && block_m == 128 ? 3 * kComputeUnits / 4 : kComputeUnits) ? 2 : 1;
+}
+
+// The same for the partial forward, whose runs each cover one chunk.
+inline int fwd_key_streams(int head_dim, int block_m, int heads_q, const Geom& g) {
+  return key_streams(head_dim, block_m, g.n / block_m * heads_q * g.P, g.ns);
 }
 
 #if defined(__HIPCC__)
@@ -134,15 +140,68 @@ __device__ inline void run_and_head(int bid, int hq, int hkv, int& run, int& h) 
   }
 }
 
+// Document start of this lane's query (global position gq), in two parts so the memory access
+// is issued at kernel start and consumed after the prologue.  With per-position starts it is one
+// load.  From the cumulative lengths instead: a wave's 32 queries (lanes 0..31; lane l ^ 32 holds
+// the query of lane l) are 32 consecutive positions -- every piece of a shard is a multiple of
+// the 64-, 128- or 256-row q-tile -- so at most 31 document boundaries lie after the document of
+// lane 0's position g_lo, up to lane 31's position g_hi.  The wave loads 64 consecutive entries
+// of cu_seqlens, starting at most 31 entries before the document of g_lo (a 64-way search in
+// rounds narrows the start when there are more than 32 entries), and each lane takes the largest
+// entry not above its position with ballots and lane reads: no further memory access.
+struct DocWindow {
+  int32_t w;           // cu[base + lane], or this lane's start when per-position starts are given
+  int32_t g_lo, g_hi;  // positions of the wave's first and last query
+};
+
+__device__ __forceinline__ DocWindow doc_window(const int32_t* doc_start, const int32_t* cu, int32_t num_docs, int32_t gq,
+                                                int lane) {
+  DocWindow r{};
+  if (!cu) {
+    r.w = doc_start[gq];
+    return r;
+  }
+  r.g_lo = __builtin_amdgcn_readlane(gq, 0);
+  r.g_hi = __builtin_amdgcn_readlane(gq, 31);
+  const int32_t nd = num_docs;
+  int32_t base = 0, len = nd + 1;  // the document of g_lo is one of base .. base + len - 1
+  while (len > 32) {
+    const int32_t stride = (len + 63) >> 6;
+    const int32_t v = cu[min(base + lane * stride, nd)];
+    base += stride * (__popcll(__builtin_amdgcn_ballot_w64(v <= r.g_lo)) - 1);
+    len = stride;
+  }
+  r.w = cu[min(base + lane, nd)];
+  return r;
+}
+
+__device__ __forceinline__ int32_t doc_window_start(const int32_t* cu, int32_t num_docs, const DocWindow& r, int32_t gq) {
+  if (!cu) return r.w;
+  const int32_t lo = __popcll(__builtin_amdgcn_ballot_w64(r.w <= r.g_lo)) - 1;    // document of g_lo
+  const int32_t last = __popcll(__builtin_amdgcn_ballot_w64(r.w <= r.g_hi)) - 1;  // last boundary <= g_hi
+  int32_t start = __builtin_amdgcn_readlane(r.w, lo);
+  if (last >= 63) {  // more boundaries than the window holds (not reachable with validated shapes)
+    int32_t l = 0, h = num_docs;
+    while (h - l > 1) {
+      const int32_t mid = (l + h) >> 1;
+      if (cu[mid] <= gq) l = mid;
+      else h = mid;
+    }
+    return cu[l];
+  }
+  for (int32_t j = lo + 1; j <= last; ++j) {
+    const int32_t b = __builtin_amdgcn_readlane(r.w, j);
+    if (gq >= b) start = b;
+  }
+  return start;
+}
+
 // The run of q-tile qt in a sorted tile list: {slot 0, qt, first, count}.
 __device__ inline hsap_run q_tile_run(const hsap_tile* tiles, int32_t num, int32_t qt, int lane) {
   const int32_t first = lower_bound_q_tile(tiles, num, qt, lane);
   const int32_t end = lower_bound_q_tile(tiles, num, qt + 1, lane);
   return hsap_run{0, qt, first, end - first};
 }
-
-// Key streams of the partial forward for the descriptor's shape.
-int fwd_key_streams(const hsap_attn_desc* d);
 
 // Workgroups of the bf16 partial forward resident on one compute unit for the descriptor's shape
 // (the runtime's occupancy of the kernel that runs); 0 when there is none.
@@ -170,12 +229,15 @@ hsap_status lse_merge(int32_t num_parts, const float* const* o_parts, const floa
 constexpr int32_t kFinalSlot = -2;
 
 // hsap_attn_bwd_bf16 with the backward preprocess folded into the dQ kernel: delta (device fp32
-// [Hq, n], written) is computed there from o and d_o, and read by the dK/dV kernel launched after.
+// [Hq, n], written) is computed there from o and d_o, and read by the dK/dV kernel launched after, and so
+// are the document starts of the shard's rows, from cu_seqlens [num_docs + 1], written to doc_start
+// [N] at the rows' positions.
 hsap_status attn_bwd_bf16_delta(const hsap_attn_desc* desc, const void* q, const void* k, const void* v,
                                 const void* d_o, const void* o, const float* lse, float* delta,
-                                const int32_t* doc_start, const hsap_tile* tiles_k, const hsap_run* runs_k,
-                                int64_t num_runs_k, const hsap_tile* tiles_q, const hsap_run* runs_q,
-                                int64_t num_runs_q, void* dq, void* dk, void* dv, hipStream_t stream);
+                                const int32_t* cu_seqlens, int32_t num_docs, int32_t* doc_start,
+                                const hsap_tile* tiles_k, const hsap_run* runs_k, int64_t num_runs_k,
+                                const hsap_tile* tiles_q, const hsap_run* runs_q, int64_t num_runs_q, void* dq,
+                                void* dk, void* dv, hipStream_t stream);
 hsap_status executor_forward(const hsap_attn_desc* desc, bool fused, const void* q, const void* k, const void* v,
                              const int32_t* cu_seqlens, int32_t num_docs, const hsap_tile* tiles,
                              const hsap_run* runs, int64_t num_runs, float* o_part, float* lse_part,
