@@ -111,7 +111,8 @@ hsap_status grow_pinned(DevBuf& b, size_t bytes) {
   b.p = nullptr;
   b.bytes = 0;
   const size_t want = std::max(bytes, size_t(4096));
-  const hipError_t e = hipHostMalloc(&b.p, want, hipHostMallocDefault);
+  // mapped and coherent: the upload kernel reads it at its host address, past the device's caches
+  const hipError_t e = hipHostMalloc(&b.p, want, hipHostMallocMapped | hipHostMallocCoherent);
   if (e != hipSuccess) {
     b.p = nullptr;
     return hip_fail("pinned allocation", e);
@@ -371,10 +372,10 @@ hsap_status hsap_executor_plan(hsap_executor* ex, const int32_t* cu_seqlens, int
   std::memcpy(h + o_cu, cu_seqlens, ((size_t)num_docs + 1) * sizeof(int32_t));
   std::memcpy(h + o_mt, ex->merged_tiles.data(), ex->merged_tiles.size() * sizeof(int32_t));
   std::memcpy(h + o_zt, ex->zero_ktiles.data(), ex->zero_ktiles.size() * sizeof(int32_t));
-  hipError_t e = hipMemcpyAsync(ex->lists.p, h, words * 4, hipMemcpyHostToDevice, stream);
-  if (e != hipSuccess) return hip_fail("list upload", e);
+  st = upload(ex->lists.p, h, words * 4, stream);
+  if (st != HSAP_OK) return st;
   if (u % kEventEvery == kEventEvery - 1) {
-    e = hipEventRecord(ex->uploaded[slot], stream);
+    const hipError_t e = hipEventRecord(ex->uploaded[slot], stream);
     if (e != hipSuccess) return hip_fail("event record", e);
     ex->event_upload[slot] = u;
   }

@@ -209,6 +209,10 @@ int fwd_resident_per_cu(const hsap_attn_desc* d);
 #endif
 
 #if defined(__HIPCC__)
+// Copies `bytes` (a multiple of 16) from pinned, device-mapped host memory to dst, both 16-byte
+// aligned, with one launch.
+hsap_status upload(void* dst, const void* pinned, size_t bytes, hipStream_t stream);
+
 // Zeroes tiles tiles[0 .. num_tiles-1] (device int32) of both a and b, tile t being the byte
 // range [t * tile_bytes, (t + 1) * tile_bytes); tile_bytes a multiple of 16, a and b 16-byte
 // aligned.  Nothing is launched for an empty list.

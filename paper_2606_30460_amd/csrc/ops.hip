@@ -394,6 +394,12 @@ __global__ __launch_bounds__(256) void quantize_convert_kernel(QuantArgs a) {
   });
 }
 
+// Copy of a list buffer out of pinned host memory, 16 bytes per thread and pass (the runtime's copy
+// of a few KB costs the host more than a launch).
+__global__ __launch_bounds__(256) void upload_kernel(uint4* dst, const uint4* src, int64_t words) {
+  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < words; i += (int64_t)gridDim.x * 256) dst[i] = src[i];
+}
+
 static hsap_status check_launch(const char* what) {
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) HSAP_FAIL(HSAP_ERR_HIP, "%s launch: %s", what, hipGetErrorString(e));
@@ -415,6 +421,16 @@ hsap_status zero_tiles(void* a, void* b, const int32_t* tiles, int32_t num_tiles
   hipLaunchKernelGGL(zero_tiles_kernel, dim3((unsigned)num_tiles, per_tile), dim3(256), 0, stream, (uint4*)a,
                      (uint4*)b, tiles, words);
   return check_launch("zero_tiles");
+}
+
+hsap_status upload(void* dst, const void* pinned, size_t bytes, hipStream_t stream) {
+  if (bytes == 0) return HSAP_OK;
+  if (!dst || !pinned || (bytes & 15) || (((uintptr_t)dst | (uintptr_t)pinned) & 15))
+    HSAP_FAIL(HSAP_ERR_INVALID_ARG, "upload: bad buffers or size %zu", bytes);
+  const int64_t words = (int64_t)(bytes / 16);
+  const unsigned blocks = (unsigned)std::min<int64_t>((words + 255) / 256, 1024);
+  hipLaunchKernelGGL(upload_kernel, dim3(blocks), dim3(256), 0, stream, (uint4*)dst, (const uint4*)pinned, words);
+  return check_launch("upload");
 }
 
 }  // namespace hsap
