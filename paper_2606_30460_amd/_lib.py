@@ -183,18 +183,35 @@ def attn_desc(shard: ShardDesc, heads_q: int, heads_kv: int, head_dim: int, soft
                     head_dim=int(head_dim), softmax_scale=float(softmax_scale))
 
 
+_torch = None                    # the torch module, once a call has needed it
+_dtypes: Dict[str, object] = {}  # its dtypes by name
+
+
+def _load_torch():
+    global _torch
+    if _torch is None:
+        import torch
+        for name in ("bfloat16", "float32", "int32", "uint8"):
+            _dtypes[name] = getattr(torch, name)
+        _torch = torch
+    return _torch
+
+
 def _ptr(a) -> int:
     """Raw address of a numpy array or torch tensor (None -> NULL)."""
     if a is None:
         return 0
     if isinstance(a, np.ndarray):
-        return a.ctypes.data
-    return int(a.data_ptr())
+        return a.__array_interface__["data"][0]
+    return a.data_ptr()
 
 
 def _stream(stream) -> int:
     if stream is None:
-        import torch
+        torch = _load_torch()
+        raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)  # (without a Stream object per call)
+        if raw is not None:
+            return raw(torch.cuda.current_device())
         return int(torch.cuda.current_stream().cuda_stream)
     if isinstance(stream, int):
         return stream
@@ -202,10 +219,11 @@ def _stream(stream) -> int:
 
 
 def _dev(t, dtype_name: str, what: str, numel: Optional[int] = None):
-    import torch
+    # (every call of every step runs this per tensor: no imports, no dtype names)
+    torch = _torch or _load_torch()
     if not isinstance(t, torch.Tensor) or not t.is_cuda:
         raise TypeError("%s must be a device tensor" % what)
-    if str(t.dtype) != "torch." + dtype_name:
+    if t.dtype is not _dtypes[dtype_name]:
         raise TypeError("%s must be %s, got %s" % (what, dtype_name, t.dtype))
     if not t.is_contiguous():
         raise ValueError("%s must be contiguous" % what)
@@ -679,7 +697,7 @@ class Executor:
         cu = cu_seqlens
         if not (isinstance(cu, np.ndarray) and cu.dtype == np.int32 and cu.flags.c_contiguous):
             cu = np.ascontiguousarray(np.asarray(cu_seqlens, dtype=np.int32))
-        _check(lib().hsap_executor_plan(self._handle(), cu.ctypes.data, len(cu) - 1, _stream(stream)))
+        _check(lib().hsap_executor_plan(self._handle(), _ptr(cu), len(cu) - 1, _stream(stream)))
 
     def info(self) -> Dict[str, int]:
         out = ExecInfo()
