@@ -78,7 +78,7 @@ constexpr int kMaxListQTiles = 2048;
 // and its dV accumulators, its dP wave the V rows and the dK accumulators.  Per
 // sub-tile of SUB query rows:
 //   scores    S wave:  S = Q K^T, P = exp2(S * scale*log2e - LSE*log2e) on
-//                      allowed pairs; P (fp16) to LDS for its partner
+//                      allowed pairs; P to LDS for its partner
 //             dP wave: dP = dO V^T
 //   products  S wave:  dV += P^T dO             (dO read transposed)
 //             dP wave: P from LDS, dS = P (dP - delta), dK += dS^T Q
@@ -129,11 +129,16 @@ __global__ __launch_bounds__(512, D == 64 && KB == 2 ? 4 : 2) void attn_bwd_dkdv
   // apart, hit different banks)
   constexpr int TILE = SUB * D;                                  // elements of one sub-tile
   constexpr int RING_BYTES = QS * RING * 2 * TILE * 2;
-  // P in fp16 (two buffers with the three-slot ring: P of t + 1 is written while the dP wave reads
-  // P of t), per pair and 32-query block: lane l's 16 values as two 16-byte pieces at [half][l]
-  // (consecutive lanes at consecutive 16 bytes: no bank conflict)
-  constexpr int PBUF = RING - 1;
-  constexpr int P_BYTES = PBUF * 4 * QB * 2 * 64 * 16;
+  // P per pair and 32-query block: lane l's 16 values as 16-byte pieces at [piece][l] (consecutive
+  // lanes at consecutive 16 bytes: no bank conflict).  KB = 4 over runs: fp16, two buffers (P of
+  // t + 1 is written while the dP wave reads P of t).  Else fp32, one buffer in the same room: in
+  // the three-slot ring, whose iterations have one barrier, a pair's S wave overwrites P of t once its
+  // dP wave has counted it as taken.  (fp32 for KB = 4 over runs costs 4 %: 131072-token step 13.96 ->
+  // 14.53 ms; elsewhere fp16 would gain 1..6 %, layer 32k of head_dim 64 871 -> 820 us, but dS would be
+  // formed from 11 bits of P.)
+  constexpr bool P32 = KB < 4 || LIST;
+  constexpr int PIECES = 4 * QB * (P32 ? 4 : 2);  // of 64 x 16 bytes, the four pairs' P of one sub-tile
+  constexpr int P_BYTES = PIECES * 64 * 16 * (P32 ? 1 : 2);
   constexpr int ACC_STRIDE = D + 8;
   constexpr int ACC_BYTES = 8 * 32 * ACC_STRIDE * 4;
   // (tile-list mode: and this k-tile's q-tiles, q_tile | kind << 31, behind the hand-off)
@@ -144,6 +149,7 @@ __global__ __launch_bounds__(512, D == 64 && KB == 2 ? 4 : 2) void attn_bwd_dkdv
   __shared__ __attribute__((aligned(16))) float ndelta_s[QS][RING][SUB];  // -delta
   __shared__ __attribute__((aligned(16))) int32_t start_s[QS][RING][SUB];
   __shared__ int32_t wave_hits[LIST ? 8 : 1];
+  __shared__ int32_t taken[4];  // fp32 hand-off, per pair: sub-tiles whose P the dP wave has read
   uint32_t* const qlist = (uint32_t*)(raw + RING_BYTES + P_BYTES);
   typedef __attribute__((address_space(3))) void* lds_void;
 
@@ -154,7 +160,8 @@ __global__ __launch_bounds__(512, D == 64 && KB == 2 ? 4 : 2) void attn_bwd_dkdv
   const int pair = w & 3;
   const int kb = pair % KB, qs = pair / KB; // key block, stream
   __bf16* const ring = (__bf16*)raw + qs * RING * 2 * TILE;  // this stream's [RING][Q | dO]
-  h16x8* const px = (h16x8*)(raw + RING_BYTES) + pair * QB * 2 * 64;  // + pbuf * 4 QB 2 64
+  using P16 = std::conditional_t<P32, f32x4, h16x8>;  // 16 bytes of P
+  P16* const px = (P16*)(raw + RING_BYTES) + pair * (PIECES / 4) * 64 + lane;
   auto q_tile = [&](int b) { return ring + b * 2 * TILE; };
   auto o_tile = [&](int b) { return ring + b * 2 * TILE + TILE; };
 
@@ -296,7 +303,7 @@ __global__ __launch_bounds__(512, D == 64 && KB == 2 ? 4 : 2) void attn_bwd_dkdv
 #pragma unroll
   for (int u = 0; u < U; ++u) {
     const int p = WCH * x + 64 * u + lane, row = p / CPR;
-    gsrc[u] = (uint32_t)((row * a.hq * D + swz_chunk<CPR>(row, p % CPR) * 8) * 2);
+    gsrc[u] = 2u * ((uint32_t)row * a.hq * D + swz_chunk<CPR>(row, p % CPR) * 8);
   }
   auto stage = [&](const __bf16* src, __bf16* dst) {
     const uint32_t lds = (uint32_t)(uintptr_t)(lds_void)dst + (uint32_t)(WCH * x * 16);
@@ -378,7 +385,7 @@ __global__ __launch_bounds__(512, D == 64 && KB == 2 ? 4 : 2) void attn_bwd_dkdv
     };
     // P of a sub-tile (register j = 4 grp + e holds query q4 + e, q4 = 32 qb + 8 grp + 4 hi;
     // P = exp2(S * scale*log2e - LSE*log2e), masked in one uniform branch): in bf16 as this wave's
-    // next A operand, in fp16 to the dP wave.
+    // next A operand, in fp32 or fp16 to the dP wave.
     auto probs = [&](int rb, f32x16 (&sp)[QB]) __attribute__((always_inline)) {
 #pragma unroll
       for (int qb = 0; qb < QB; ++qb)
@@ -390,7 +397,7 @@ __global__ __launch_bounds__(512, D == 64 && KB == 2 ? 4 : 2) void attn_bwd_dkdv
             sp[qb][4 * grp + e] = fast_exp2(__builtin_fmaf(sp[qb][4 * grp + e], a.scale_log2, -l4[e]));
         }
     };
-    auto hand_over = [&](int rb, int pbuf, const Pos& ps, f32x16 (&sp)[QB], bf16x8 (&opnd)[QB][2])
+    auto hand_over = [&](int rb, int t, const Pos& ps, f32x16 (&sp)[QB], bf16x8 (&opnd)[QB][2])
                          __attribute__((always_inline)) {
       if (ps.masked) {
 #pragma unroll
@@ -406,31 +413,58 @@ __global__ __launch_bounds__(512, D == 64 && KB == 2 ? 4 : 2) void attn_bwd_dkdv
       }
 #pragma unroll
       for (int qb = 0; qb < QB; ++qb) {
+        if constexpr (P32) {
 #pragma unroll
-        for (int half = 0; half < 2; ++half) {
-          h16x8 ph;
+          for (int grp = 0; grp < 4; ++grp)
+            px[(qb * 4 + grp) * 64] =
+                f32x4{sp[qb][4 * grp], sp[qb][4 * grp + 1], sp[qb][4 * grp + 2], sp[qb][4 * grp + 3]};
+        } else {
 #pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            const auto pk = __builtin_amdgcn_cvt_pkrtz(sp[qb][8 * half + 2 * i], sp[qb][8 * half + 2 * i + 1]);
-            ph[2 * i] = pk[0];
-            ph[2 * i + 1] = pk[1];
+          for (int half = 0; half < 2; ++half) {
+            h16x8 ph;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+              const auto pk = __builtin_amdgcn_cvt_pkrtz(sp[qb][8 * half + 2 * i], sp[qb][8 * half + 2 * i + 1]);
+              ph[2 * i] = pk[0];
+              ph[2 * i + 1] = pk[1];
+            }
+            px[((t & 1) * PIECES + qb * 2 + half) * 64] = ph;
           }
-          px[(pbuf * 4 * QB + qb) * 128 + half * 64 + lane] = ph;
         }
 #pragma unroll
         for (int j = 0; j < 16; ++j) opnd[qb][j >> 3][j & 7] = (__bf16)sp[qb][j];
       }
     };
-    // dS = P (dP - delta) of a sub-tile: one mixed-precision multiply per element (fp16 P)
-    auto take_over = [&](int pbuf, const f32x16 (&sp)[QB], bf16x8 (&opnd)[QB][2]) __attribute__((always_inline)) {
+    // dS = P (dP - delta) of sub-tile t (fp16: one mixed-precision multiply per element).  An fp32 P
+    // counts as taken once it is read: a wave's LDS operations are carried out in the order they are
+    // issued, which the empty asm keeps, so no wait stands between.
+    auto take_over = [&](int t, const f32x16 (&sp)[QB], bf16x8 (&opnd)[QB][2]) __attribute__((always_inline)) {
 #pragma unroll
       for (int qb = 0; qb < QB; ++qb) {
-        const h16x8 ph[2] = {px[(pbuf * 4 * QB + qb) * 128 + lane], px[(pbuf * 4 * QB + qb) * 128 + 64 + lane]};
+        if constexpr (P32) {
 #pragma unroll
-        for (int j = 0; j < 16; ++j)
-          opnd[qb][j >> 3][j & 7] = (__bf16)__builtin_fmaf((float)ph[j >> 3][j & 7], sp[qb][j], 0.f);
+          for (int grp = 0; grp < 4; ++grp) {
+            const f32x4 p = px[(qb * 4 + grp) * 64];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+              const int j = 4 * grp + e;
+              opnd[qb][j >> 3][j & 7] = (__bf16)(p[e] * sp[qb][j]);
+            }
+          }
+        } else {
+          const h16x8 ph[2] = {px[((t & 1) * PIECES + qb * 2) * 64], px[((t & 1) * PIECES + qb * 2 + 1) * 64]};
+#pragma unroll
+          for (int j = 0; j < 16; ++j)
+            opnd[qb][j >> 3][j & 7] = (__bf16)__builtin_fmaf((float)ph[j >> 3][j & 7], sp[qb][j], 0.f);
+        }
+      }
+      if constexpr (P32 && RING == 3) {
+        asm volatile("" ::: "memory");
+        __hip_atomic_store(&taken[pair], t + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        asm volatile("" ::: "memory");
       }
     };
+    auto taken_now = [&] { return __hip_atomic_load(&taken[pair], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP); };
     // Gradient products of a sub-tile (buffer tb): dV += P^T dO or dK += dS^T Q, dO and Q read
     // transposed, 16 queries per MFMA
     auto products = [&](int tb, const bf16x8 (&opnd)[QB][2]) __attribute__((always_inline)) {
@@ -448,6 +482,7 @@ __global__ __launch_bounds__(512, D == 64 && KB == 2 ? 4 : 2) void attn_bwd_dkdv
         }
     };
     // prologue: the first sub-tiles staged, the scores of sub-tile 0
+    if (P32 && S && lane == 0) taken[pair] = 0;
     ensure_window(0);
     Pos cur{0, 0, qs, false, false, 0};
     if (QS > 2 && nsub < QS) {
@@ -488,15 +523,22 @@ __global__ __launch_bounds__(512, D == 64 && KB == 2 ? 4 : 2) void attn_bwd_dkdv
         const bool more = t + 2 < total;
         if (more) load_sub(nx2, b2);  // buffer b2 was last read before the previous barrier
         if constexpr (S) {
+          int32_t seen = P32 ? taken_now() : 0;
           products(b0, opnd);
+          if constexpr (P32) {
+            // P of t is taken at the start of the partner's iteration, before any barrier of its own:
+            // mostly done by now, and the wait ends whatever the order of the two waves
+            while (__builtin_amdgcn_readfirstlane(seen) <= t) seen = taken_now();
+            asm volatile("" ::: "memory");
+          }
           scores(b1, sp);
           probs(b1, sp);
-          hand_over(b1, (t + 1) & 1, nx1, sp, opnd);
+          hand_over(b1, t + 1, nx1, sp, opnd);
         } else {
           // dS leaves sp, so the dP products of t + 1 go first: their row reads and the dS
           // arithmetic fill the shadow of the S wave's products, and dK follows (against dK first:
           // 131072-token step 14.71 -> 14.43 ms, 32768-token step 624 -> 615 us)
-          take_over(t & 1, sp, opnd);
+          take_over(t, sp, opnd);
           scores(b1, sp);
           products(b0, opnd);
         }
@@ -506,26 +548,26 @@ __global__ __launch_bounds__(512, D == 64 && KB == 2 ? 4 : 2) void attn_bwd_dkdv
         nx1 = nx2;
         b0 = b1;
       }
-      if constexpr (!S) take_over((total - 1) & 1, sp, opnd);
+      if constexpr (!S) take_over(total - 1, sp, opnd);
       products(b0, opnd);
     } else {
       // Two buffers: sub-tile t + 1 moves into the buffer of t - 1 while the products of t run.
       for (int t = 0; t + 1 < total; ++t) {
         const int b0 = t & 1, b1 = b0 ^ 1;
         load_sub(nx1, b1);
-        if constexpr (!S) take_over(0, sp, opnd);
+        if constexpr (!S) take_over(t, sp, opnd);
         products(b0, opnd);
         store_sub(b1);
         asm volatile("s_waitcnt vmcnt(0)\n\ts_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
         scores(b1, sp);
         if constexpr (S) {
           probs(b1, sp);
-          hand_over(b1, 0, nx1, sp, opnd);
+          hand_over(b1, t + 1, nx1, sp, opnd);
         }
         hsap_lds_barrier();  // P of t + 1 is in LDS; every read of buffer b0 is done
         nx1 = advance(nx1);
       }
-      if constexpr (!S) take_over(0, sp, opnd);
+      if constexpr (!S) take_over(total - 1, sp, opnd);
       products((total - 1) & 1, opnd);
     }
 
@@ -898,7 +940,9 @@ static hsap_status launch_dkdv(const BwdArgs& a, int d, int64_t num_runs, hipStr
     return launch_dkdv_kb<64, 2, BF16OUT, LIST>(a, num_runs, stream);
   }
   if (one) return launch_dkdv_kb<128, 1, BF16OUT, LIST>(a, num_runs, stream);
-  if (a.bn == 64 || blocks <= 4 * kComputeUnits) return launch_dkdv_kb<128, 2, BF16OUT, LIST>(a, num_runs, stream);
+  // (a 64-row sub-tile has to fit 32-bit byte offsets)
+  if (a.bn == 64 || blocks <= 4 * kComputeUnits || (int64_t)a.hq * d * 64 > INT32_MAX)
+    return launch_dkdv_kb<128, 2, BF16OUT, LIST>(a, num_runs, stream);
   return launch_dkdv_kb<128, 4, BF16OUT, LIST>(a, num_runs, stream);
 }
 
@@ -958,7 +1002,8 @@ static hsap_status backward(const hsap_attn_desc* desc, const void* q, const voi
   const int bm = desc->shard.block_m, bn = desc->shard.block_n, d = desc->head_dim;
   if (!backward_supported(desc))
     HSAP_FAIL(HSAP_ERR_UNSUPPORTED, "no backward kernel for head_dim=%d BM=%d BN=%d", d, bm, bn);
-  if ((int64_t)desc->heads_kv * d * 64 > INT32_MAX) HSAP_FAIL(HSAP_ERR_UNSUPPORTED, "heads_kv too large");
+  if ((int64_t)desc->heads_kv * d * 64 > INT32_MAX || (int64_t)desc->heads_q * d * 32 > INT32_MAX)
+    HSAP_FAIL(HSAP_ERR_UNSUPPORTED, "too many heads");
   // the dQ kernel packs a tile descriptor as k_tile | chunk << 23 | kind << 31
   if (num_runs_q > 0 && (geom.P > kMaxDqChunks || geom.n / bn >= kMaxDqKTiles))
     HSAP_FAIL(HSAP_ERR_UNSUPPORTED, "the dQ kernel needs sp_degree <= %d and fewer than 2^23 k-tiles per chunk "
@@ -1046,7 +1091,8 @@ static hsap_status backward_tile_list(const hsap_attn_desc* desc, const void* q,
   const int bm = desc->shard.block_m, bn = desc->shard.block_n, d = desc->head_dim;
   if (!backward_supported(desc))
     HSAP_FAIL(HSAP_ERR_UNSUPPORTED, "no backward kernel for head_dim=%d BM=%d BN=%d", d, bm, bn);
-  if ((int64_t)desc->heads_kv * d * 64 > INT32_MAX) HSAP_FAIL(HSAP_ERR_UNSUPPORTED, "heads_kv too large");
+  if ((int64_t)desc->heads_kv * d * 64 > INT32_MAX || (int64_t)desc->heads_q * d * 32 > INT32_MAX)
+    HSAP_FAIL(HSAP_ERR_UNSUPPORTED, "too many heads");
   if (desc->chunk_id < 0 || desc->chunk_id >= geom.P)
     HSAP_FAIL(HSAP_ERR_INVALID_ARG, "chunk_id %d outside [0, %d)", desc->chunk_id, geom.P);
   if (num_tiles < 0 || num_tiles > (int64_t(1) << 30))

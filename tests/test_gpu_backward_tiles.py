@@ -51,6 +51,19 @@ def test_backward_workgroup_shapes(case):
             assert err <= 2.0 ** -7, (case, key, err)
 
 
+@pytest.mark.parametrize("case", CASES[:7])
+def test_dk_keeps_p_in_32_bits(case):
+    # dS = P (dP - delta) from P in fp32: bf16 roundings (to nearest) leave the component of dK along the
+    # exact one at 1 up to 0.003 / sqrt(elements) < 1e-5; a P cut to the 11 bits of fp16 loses
+    # 2^-12 of it on average (2.4e-4).  (The executor's 128-key workgroups, CASES[3], do hold fp16.)
+    c = _case(*case)
+    ref = c.run_oracle()["dk"]
+    outs = [c.run_tile_list()] + ([c.run_executor()] if case != CASES[3] else [])
+    for got in outs:
+        along = float(np.sum(got["dk"].astype(np.float64) * ref) / np.sum(np.square(ref, dtype=np.float64)))
+        assert abs(along - 1.0) <= 2.0 ** -14, (case, along)
+
+
 @pytest.mark.parametrize("case", [CASES[1], CASES[5]])
 def test_backward_unaligned_outputs(case):
     # dK and dV 2 bytes (fp32 accumulators: 4 bytes) off a 16-byte boundary give the aligned bits
