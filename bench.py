@@ -448,7 +448,7 @@ def fwd_source_hash() -> str:
 def fwd_kernel_name(res) -> str:
     """The partial forward kernel the library dispatches for a workload's shapes (bf16 scores)."""
     d, bm, bn = res["head_dim"], res["block_m"], res["block_n"]
-    return "attn_fwd_dl_kernel<%d, %d, %d, false, false, false>" % (d, bn, bm // 32)
+    return "attn_fwd_dl_kernel<%d, %d, %d, false, false, false, 1>" % (d, bn, bm // 32)
 
 
 def bwd_kernel_names(res) -> list:
@@ -456,7 +456,7 @@ def bwd_kernel_names(res) -> list:
     of more than 1024 blocks of 32 keys, as every workload's here)."""
     d, bm, bn = res["head_dim"], res["block_m"], res["block_n"]
     dkdv = "attn_bwd_dkdv_kernel<%d, %d, true, false>" % (d, 4 if d == 128 and bn == 128 else 2)
-    return [dkdv, "attn_bwd_dq_kernel<%d, %d, %d, true, false>" % (d, bn, bm // 32)]
+    return [dkdv, "attn_bwd_dq_kernel<%d, %d, %d, true, false, 1>" % (d, bn, bm // 32)]
 
 
 def measured_traffic(workload: str):
