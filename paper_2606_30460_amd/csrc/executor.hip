@@ -242,7 +242,9 @@ hsap_status hsap_executor_plan(hsap_executor* ex, const int32_t* cu_seqlens, int
   // run there is by much: it is left out unless that run holds more than four times the average.
   // Forward + merge with and without it: 32768 tokens, runs of up to 11 tiles for an average of 5.4: 48.1 and
   // 38.8 us; 32 tiles for 14.2: 50.9 and 44.4 us; 8 tiles for 0.1 (one head): 18.2 and 20.2 us; 9 tiles for 2.3
-  // (2048 tokens x 4 heads of 64, one chunk): 12.6 and 9.8 us.
+  // (2048 tokens x 4 heads of 64, one chunk): 12.6 and 9.8 us.  Of 21 random forwards of 20..115 us whose split
+  // the line drops, two lost 10 % (31 tiles for 9.5: 43.8 -> 48.8 us; 8 for 3.6 at 256-row q-tiles: 41.0 -> 45.5 us)
+  // and four 1..5 %, three stayed, twelve gained 2..36 %.
   if (ex->max_run_tiles < 0 && split > 0) {
     int64_t longest = 0, len = 0;  // the tiles are in (ring step, q-tile, k-tile) order
     for (int64_t i = 0; i < T; ++i) {
