@@ -111,7 +111,9 @@ constexpr int kMaxListQTiles = 2048;
 // (sub-tile t + 1 is moved during the products of t, with a barrier between
 // the products and the scores).
 // ---------------------------------------------------------------------------
-template <int D, int KB, bool BF16OUT, bool LIST>
+// WIDE: Q rows of so many heads that 32 of them do not fit 32-bit byte offsets (the transfers take
+// 64-bit addresses per lane).
+template <int D, int KB, bool BF16OUT, bool LIST, bool WIDE = false>
 __global__ __launch_bounds__(512, D == 64 && KB == 2 ? 4 : 2) void attn_bwd_dkdv_kernel(BwdArgs a) {
   static_assert(!LIST || !BF16OUT, "the tile-list mode accumulates fp32");
   static_assert((D == 128 || D == 64) && (KB == 4 || KB == 2 || KB == 1), "shapes with a kernel");
@@ -300,17 +302,21 @@ __global__ __launch_bounds__(512, D == 64 && KB == 2 ? 4 : 2) void attn_bwd_dkdv
   // swizzle places there, a 32-bit byte offset from the sub-tile's scalar base (Q and dO rows have
   // the same stride)
   const int x = kb + (s_wave ? 0 : KB);
-  uint32_t gsrc[U];
+  using Offset = std::conditional_t<WIDE, uint64_t, uint32_t>;
+  Offset gsrc[U];
 #pragma unroll
   for (int u = 0; u < U; ++u) {
     const int p = WCH * x + 64 * u + lane, row = p / CPR;
-    gsrc[u] = 2u * ((uint32_t)row * a.hq * D + swz_chunk<CPR>(row, p % CPR) * 8);
+    gsrc[u] = 2u * ((Offset)row * a.hq * D + swz_chunk<CPR>(row, p % CPR) * 8);
   }
   auto stage = [&](const __bf16* src, __bf16* dst) {
     const uint32_t lds = (uint32_t)(uintptr_t)(lds_void)dst + (uint32_t)(WCH * x * 16);
 #pragma unroll
     for (int u = 0; u < U; ++u)
-      asm volatile("global_load_lds_dwordx4 %0, %1" ::"v"(gsrc[u]), "s"(src), "{m0}"(lds + 64 * 16 * u));
+      if constexpr (WIDE)
+        asm volatile("global_load_lds_dwordx4 %0, off" ::"v"((const char*)src + gsrc[u]), "{m0}"(lds + 64 * 16 * u));
+      else
+        asm volatile("global_load_lds_dwordx4 %0, %1" ::"v"(gsrc[u]), "s"(src), "{m0}"(lds + 64 * 16 * u));
   };
   // One role's whole run (S: K rows and dV; otherwise V rows and dK).  The two loops are separate
   // code, so each is one straight-line block per iteration for the compiler to order.
@@ -915,12 +921,12 @@ __global__ __launch_bounds__(64 * WAVES * KS, 2) void attn_bwd_dq_kernel(BwdArgs
     }
 }
 
-template <int D, int KB, bool BF16OUT, bool LIST>
+template <int D, int KB, bool BF16OUT, bool LIST, bool WIDE = false>
 static hsap_status launch_dkdv_kb(BwdArgs a, int64_t num_runs, hipStream_t stream) {
   a.parts = a.bn / (32 * KB);
   const int64_t blocks = num_runs * a.parts * a.hkv;
   if (blocks > INT32_MAX) HSAP_FAIL(HSAP_ERR_INVALID_ARG, "too many runs x heads");
-  hipLaunchKernelGGL((attn_bwd_dkdv_kernel<D, KB, BF16OUT, LIST>), dim3((unsigned)blocks), dim3(512), 0, stream, a);
+  hipLaunchKernelGGL((attn_bwd_dkdv_kernel<D, KB, BF16OUT, LIST, WIDE>), dim3((unsigned)blocks), dim3(512), 0, stream, a);
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) HSAP_FAIL(HSAP_ERR_HIP, "attn_bwd_dkdv launch: %s", hipGetErrorString(e));
   return HSAP_OK;
@@ -936,6 +942,9 @@ template <bool BF16OUT, bool LIST = false>
 static hsap_status launch_dkdv(const BwdArgs& a, int d, int64_t num_runs, hipStream_t stream) {
   const int64_t blocks = num_runs * (a.bn / 32) * a.hkv;
   const bool one = blocks <= 2 * kComputeUnits;
+  if ((int64_t)a.hq * d * 32 > INT32_MAX)
+    return d == 64 ? launch_dkdv_kb<64, 2, BF16OUT, LIST, true>(a, num_runs, stream)
+                   : launch_dkdv_kb<128, 2, BF16OUT, LIST, true>(a, num_runs, stream);
   if (d == 64) {
     if (one) return launch_dkdv_kb<64, 1, BF16OUT, LIST>(a, num_runs, stream);
     return launch_dkdv_kb<64, 2, BF16OUT, LIST>(a, num_runs, stream);
@@ -1003,8 +1012,7 @@ static hsap_status backward(const hsap_attn_desc* desc, const void* q, const voi
   const int bm = desc->shard.block_m, bn = desc->shard.block_n, d = desc->head_dim;
   if (!backward_supported(desc))
     HSAP_FAIL(HSAP_ERR_UNSUPPORTED, "no backward kernel for head_dim=%d BM=%d BN=%d", d, bm, bn);
-  if ((int64_t)desc->heads_kv * d * 64 > INT32_MAX || (int64_t)desc->heads_q * d * 32 > INT32_MAX)
-    HSAP_FAIL(HSAP_ERR_UNSUPPORTED, "too many heads");
+  if ((int64_t)desc->heads_kv * d * 64 > INT32_MAX) HSAP_FAIL(HSAP_ERR_UNSUPPORTED, "heads_kv too large");
   // the dQ kernel packs a tile descriptor as k_tile | chunk << 23 | kind << 31
   if (num_runs_q > 0 && (geom.P > kMaxDqChunks || geom.n / bn >= kMaxDqKTiles))
     HSAP_FAIL(HSAP_ERR_UNSUPPORTED, "the dQ kernel needs sp_degree <= %d and fewer than 2^23 k-tiles per chunk "
@@ -1092,8 +1100,7 @@ static hsap_status backward_tile_list(const hsap_attn_desc* desc, const void* q,
   const int bm = desc->shard.block_m, bn = desc->shard.block_n, d = desc->head_dim;
   if (!backward_supported(desc))
     HSAP_FAIL(HSAP_ERR_UNSUPPORTED, "no backward kernel for head_dim=%d BM=%d BN=%d", d, bm, bn);
-  if ((int64_t)desc->heads_kv * d * 64 > INT32_MAX || (int64_t)desc->heads_q * d * 32 > INT32_MAX)
-    HSAP_FAIL(HSAP_ERR_UNSUPPORTED, "too many heads");
+  if ((int64_t)desc->heads_kv * d * 64 > INT32_MAX) HSAP_FAIL(HSAP_ERR_UNSUPPORTED, "heads_kv too large");
   if (desc->chunk_id < 0 || desc->chunk_id >= geom.P)
     HSAP_FAIL(HSAP_ERR_INVALID_ARG, "chunk_id %d outside [0, %d)", desc->chunk_id, geom.P);
   if (num_tiles < 0 || num_tiles > (int64_t(1) << 30))

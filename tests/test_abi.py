@@ -245,6 +245,19 @@ def test_backward_rejects_dq_beyond_packed_descriptors():
         assert "256" in lib.hsap_last_error().decode()
 
 
+@pytest.mark.parametrize("dim,heads_q", [(64, 1 << 20), (128, 1 << 19)])
+def test_backward_accepts_q_rows_beyond_32_bit_sub_tiles(dim, heads_q):
+    # 32 Q rows of so many heads span 4 GiB: no bound on heads_q but memory's (and the grid's)
+    lib = L.lib()
+    fake = ctypes.c_void_p(4096)
+    d = _attn_desc(total_tokens=64, sp_degree=1, block_m=64, block_n=64, head_dim=dim, heads_q=heads_q, heads_kv=1 << 17)
+    for fn in (lib.hsap_partial_attn_bwd_runs, lib.hsap_attn_bwd_bf16):
+        assert fn(ctypes.byref(d), fake, fake, fake, fake, fake, fake, fake, fake, fake, 0, fake, fake, 0, fake, fake,
+                  fake, None) == L.HSAP_OK, lib.hsap_last_error().decode()   # nothing to do
+    assert lib.hsap_partial_attn_bwd(ctypes.byref(d), fake, fake, fake, fake, fake, fake, fake, None, 0, fake, fake,
+                                     fake, None) == L.HSAP_OK, lib.hsap_last_error().decode()
+
+
 def test_backward_shapes_of_256_row_tiles():
     # 256-row q-tiles have a backward for head_dim 128 only; a rejected shape launches nothing
     lib = L.lib()

@@ -95,3 +95,46 @@ def test_backward_unaligned_outputs(case):
     ex.close()
     for a, b in zip(got[0], got[1]):
         assert torch.equal(a, b)
+
+
+def test_backward_q_rows_beyond_32_bit_offsets():
+    # 2^20 query heads of 64: 32 Q rows are 4 GiB, so the dK/dV kernel's transfers take 64-bit addresses.
+    # The heads repeat a block of 64 (16 K/V heads), so every block has to give the bits of the first, and the
+    # first what a call over that block alone gives (other workgroup shapes: bf16 P, dS and results, 2^-7)
+    from paper_2606_30460_amd import _lib as L
+    N, D, hq, hkv, reps = 64, 64, 64, 16, 1 << 14
+    dev = torch.device("cuda")
+    g = torch.Generator(device="cuda").manual_seed(0)
+    small = [torch.randn(N, h, D, generator=g, device=dev).to(torch.bfloat16) for h in (hq, hkv, hkv, hq)]
+    lse_s = torch.full((hq, N), 4.0, device=dev)
+    delta_s = torch.randn(hq, N, generator=g, device=dev)
+    cu = np.asarray([0, N], dtype=np.int32)
+    doc_start = torch.zeros(N, dtype=torch.int32, device=dev)
+    got = {}
+    for r in (1, reps):
+        s = L.shard_desc(N, 1, "contiguous", 0, 64, 64)
+        desc = L.attn_desc(s, hq * r, hkv * r, D, D ** -0.5)
+        tiles = L.plan(cu, s)["tiles"]
+        lists = [torch.from_numpy(np.ascontiguousarray(x).reshape(-1)).to(dev)
+                 for m in (L.MAJOR_K, L.MAJOR_Q_ALL) for x in L.plan_runs(s, tiles, m, 0)[:2]]
+        q, k, v, d_o = (x.repeat(1, r, 1) for x in small)
+        lse, delta = lse_s.repeat(r, 1), delta_s.repeat(r, 1)
+        for fp32 in (False, True):
+            t = torch.float32 if fp32 else torch.bfloat16
+            dq, dk, dv = (torch.zeros(x.shape, dtype=t, device=dev) for x in (q, k, v))
+            if fp32:
+                L.partial_attn_bwd(desc, q, k, v, d_o, lse, delta, doc_start, torch.from_numpy(tiles).to(dev), dq, dk, dv)
+            else:
+                L.attn_bwd_bf16(desc, q, k, v, d_o, lse, delta, doc_start, *lists, dq, dk, dv)
+            for name, x, h in (("dq", dq, hq), ("dk", dk, hkv), ("dv", dv, hkv)):
+                first = x[:, :h].contiguous()
+                for i in range(0, r, 1024):     # (in pieces: the comparison's own buffers stay small)
+                    part = x[:, i * h:min(r, i + 1024) * h].view(N, -1, h, D)
+                    assert torch.equal(part, first.unsqueeze(1).expand_as(part)), (name, fp32, r, i)
+                got[name, fp32, r] = first.float()
+            del dq, dk, dv
+        del q, k, v, d_o, lse, delta
+    for name in ("dq", "dk", "dv"):
+        for fp32 in (False, True):
+            a, b = got[name, fp32, 1], got[name, fp32, reps]
+            assert float((a - b).norm() / a.norm()) <= 2.0 ** -7, (name, fp32)
