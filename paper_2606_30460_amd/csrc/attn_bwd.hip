@@ -258,13 +258,15 @@ __global__ __launch_bounds__(512, D == 64 && KB == 2 ? 4 : 2) void attn_bwd_dkdv
   // Sub-tile position as counters (no division in the loop): query head h, tile index idx in the
   // run, SUB-row slice sb of the tile; with its position and kind once it has been loaded.  Stream qs
   // takes the slices qs, qs + QS, ... of every tile or, of tiles with fewer slices (64-row q-tiles,
-  // four streams), slice qs % nsub of every other tile; there its last iteration may lie past the
-  // run's end, and then it repeats the last sub-tile with P = 0.
+  // four streams), slice qs % nsub of every other tile; there its last iteration lies past the run's
+  // end when the tiles are odd in number: it moves the last sub-tile once more and leaves its
+  // products out (`past`; P = 0 would turn an infinite dO of that sub-tile into NaN).
   struct Pos {
     int h, idx, sb;
-    bool past, masked;
+    bool masked;
     int32_t gq0;
   };
+  const bool past = QS > 2 && nsub < QS && qs >= nsub && (a.group * count) % 2 != 0;
   auto fold = [&](Pos p) {  // tile indexes past the run's end continue with the next query head
     if (p.idx >= count) {
       p.idx -= count;
@@ -275,7 +277,6 @@ __global__ __launch_bounds__(512, D == 64 && KB == 2 ? 4 : 2) void attn_bwd_dkdv
       }
     }
     if (QS > 2 && p.h >= a.group) {
-      p.past = true;
       p.h = a.group - 1;
       p.idx = count - 1;
     }
@@ -351,7 +352,7 @@ __global__ __launch_bounds__(512, D == 64 && KB == 2 ? 4 : 2) void attn_bwd_dkdv
       stage(a.q + base, q_tile(buf));
       stage(a.d_o + base, o_tile(buf));
       if (row_lane) {
-        lreg = ps.past ? -__builtin_inff() : a.lse[(int64_t)h * n + q0 + lane];
+        lreg = a.lse[(int64_t)h * n + q0 + lane];
         dreg = a.delta[(int64_t)h * n + q0 + lane];
         sreg = a.doc_start[ps.gq0 + lane];
       }
@@ -491,7 +492,7 @@ __global__ __launch_bounds__(512, D == 64 && KB == 2 ? 4 : 2) void attn_bwd_dkdv
     // prologue: the first sub-tiles staged, the scores of sub-tile 0
     if (P32 && S && lane == 0) taken[pair] = 0;
     ensure_window(0);
-    Pos cur{0, 0, qs, false, false, 0};
+    Pos cur{0, 0, qs, false, 0};
     if (QS > 2 && nsub < QS) {
       cur.sb = qs % 2;
       cur.idx = qs / 2;
@@ -555,8 +556,10 @@ __global__ __launch_bounds__(512, D == 64 && KB == 2 ? 4 : 2) void attn_bwd_dkdv
         nx1 = nx2;
         b0 = b1;
       }
-      if constexpr (!S) take_over(total - 1, sp, opnd);
-      products(b0, opnd);
+      if (!past) {
+        if constexpr (!S) take_over(total - 1, sp, opnd);
+        products(b0, opnd);
+      }
     } else {
       // Two buffers: sub-tile t + 1 moves into the buffer of t - 1 while the products of t run.
       for (int t = 0; t + 1 < total; ++t) {
@@ -574,8 +577,10 @@ __global__ __launch_bounds__(512, D == 64 && KB == 2 ? 4 : 2) void attn_bwd_dkdv
         hsap_lds_barrier();  // P of t + 1 is in LDS; every read of buffer b0 is done
         nx1 = advance(nx1);
       }
-      if constexpr (!S) take_over(total - 1, sp, opnd);
-      products((total - 1) & 1, opnd);
+      if (!past) {
+        if constexpr (!S) take_over(total - 1, sp, opnd);
+        products((total - 1) & 1, opnd);
+      }
     }
 
     // the accumulators to LDS, once no wave reads the ring or P any more

@@ -97,6 +97,18 @@ def test_backward_unaligned_outputs(case):
         assert torch.equal(a, b)
 
 
+@pytest.mark.parametrize("d", [64, 128])
+def test_infinite_do_stays_infinite(d):
+    # a run of three 64-row q-tiles over four streams of sub-tiles: two streams end past the run.  An
+    # infinite dO in the last row gives infinities in dV of the k-tiles that lie wholly below it (every
+    # P > 0 there), and no NaN
+    c = _case(192, 1, 1, d, 64, 64, [192])
+    c.do[191, 0, :] = float("inf")
+    for got in (c.run_executor(), c.run_tile_list()):
+        dv = got["dv"].reshape(-1, d)
+        assert np.isposinf(dv[:128]).all(), (d, np.isnan(dv[:128]).sum())
+
+
 def test_backward_q_rows_beyond_32_bit_offsets():
     # 2^20 query heads of 64: 32 Q rows are 4 GiB, so the dK/dV kernel's transfers take 64-bit addresses.
     # The heads repeat a block of 64 (16 K/V heads), so every block has to give the bits of the first, and the
