@@ -426,8 +426,8 @@ hsap_status hsap_partial_attn_fwd(const hsap_attn_desc* desc, const void* q, con
  *   dk_acc, dv_acc  device fp32 [P, n, Hkv, d] sharded order (+=): the rows
  *              of chunk c's k-tiles that have a tile (a caller holding chunk c
  *              alone may pass the address chunk 0 would have).
- * Two launches on `stream` (dQ: (n / BM) x Hq workgroups; dK/dV: (n / BN) x
- * Hkv workgroups, each scanning the list for its k-tile).  The caller zeroes
+ * Two launches on `stream` (dQ: (n / BM) x Hq workgroups; dK/dV: one to four
+ * per k-tile and K/V head, each scanning the list for its k-tile).  The caller zeroes
  * the accumulators once; one call per chunk of a ring accumulates dQ over the
  * ring.  Errors as for hsap_partial_attn_fwd.  For the gradients of every
  * chunk at once, the run-based entry points below avoid the per-k-tile scans.
@@ -626,6 +626,9 @@ hsap_status hsap_attn_bwd_preprocess(const void* o, const void* d_o, int64_t n, 
  *              workgroup: plain read-modify-write.
  *   The caller zeroes the accumulators once; concurrent calls on the same
  *   accumulators race.
+ * How a workgroup divides a k-tile or q-tile (and so the order of its sums)
+ * follows from `desc` alone: runs passed in one call or in several give the
+ * same bits.
  */
 hsap_status hsap_partial_attn_bwd_runs(const hsap_attn_desc* desc, const void* q, const void* k,
                                   const void* v, const void* d_o, const float* lse,

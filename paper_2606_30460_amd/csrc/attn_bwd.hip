@@ -937,16 +937,31 @@ static hsap_status launch_dkdv_kb(BwdArgs a, int64_t num_runs, hipStream_t strea
   return HSAP_OK;
 }
 
-// Key blocks of 32 per dK/dV workgroup, from the number of them in the whole call (one workgroup per
-// CU is resident, at head_dim 64 two of 64 keys).  Fewer key blocks per workgroup give more, shorter
-// workgroups at more staging traffic per product, which pays as long as they are at most about two
-// per CU.  Measured at one causal document, head_dim 128 (us for 128 / 64 / 32 keys per workgroup):
-// 512 blocks 111.9 / 84.1 / 62.4, 1024 blocks 115.4 / 98.9 / 120.2, 2048 blocks 152.3 / 194.2 / 247.3;
-// head_dim 64 (64 / 32 keys): 512 blocks 66.3 / 46.2, 1024 blocks 71.5 / 88.6.
+// k-tiles of the whole K/V that the shard's queries can reach under the causal mask (all their documents
+// being one): per sequence, the keys up to the shard's last row.
+static int64_t reachable_k_tiles(const Geom& g, int32_t shard, int32_t bn) {
+  const int64_t keys = (g.layout == HSAP_LAYOUT_CONTIGUOUS ? shard + 1 : 2 * g.P - shard) * g.m;
+  return g.B * ((keys + bn - 1) / bn);
+}
+
+// Key blocks of 32 per dK/dV workgroup (one workgroup per CU is resident, at head_dim 64 two of 64 keys).
+// Fewer key blocks per workgroup give more, shorter workgroups at more staging traffic per product,
+// which pays while the grid leaves the chip idle.  The choice depends on the descriptor alone -- the key
+// blocks the shard can reach (tile-list call: those of its chunk) -- so that calls over the same tiles give
+// the same bits however their lists are cut and whichever other tiles share the call.  Over 600 random
+// backwards (dQ included; geometric mean of the gain against one wave per 32 keys at 64-key tiles, 128
+// keys per workgroup at 128-key tiles; in brackets the worst of them):
+//   128-key tiles, 128 or 32 keys a workgroup:  32 up to 512 reachable blocks 1.21 (0.97), 640 1.22 (0.97), 768 1.23
+//     (0.86), 1024 1.22 (0.75).  (64 keys from 513 to 1024 blocks: down to 0.86, two workgroups in turn on most CUs)
+//   64-key tiles, 64 or 32 keys:  512 blocks 1.44 / 1.51 at head_dim 128 / 64, 768 1.45 / 1.53 (0.98), 1024 1.45 / 1.53,
+//     1536 1.44 / 1.52 (0.90)
+// Tile-list calls at one causal document, head_dim 128 (us for 128 / 64 / 32 keys): 512 blocks 111.9 / 84.1 / 62.4,
+// 1024 blocks 115.4 / 98.9 / 120.2, 2048 blocks 152.3 / 194.2 / 247.3; head_dim 64 (64 / 32 keys): 512 blocks
+// 66.3 / 46.2, 1024 blocks 71.5 / 88.6.
 template <bool BF16OUT, bool LIST = false>
 static hsap_status launch_dkdv(const BwdArgs& a, int d, int64_t num_runs, hipStream_t stream) {
-  const int64_t blocks = num_runs * (a.bn / 32) * a.hkv;
-  const bool one = blocks <= 2 * kComputeUnits;
+  const int64_t blocks = (LIST ? num_runs : reachable_k_tiles(a.geom, a.shard, a.bn)) * (a.bn / 32) * a.hkv;
+  const bool one = blocks <= (LIST ? 512 : a.bn == 128 ? 640 : 768);
   if ((int64_t)a.hq * d * 32 > INT32_MAX)
     return d == 64 ? launch_dkdv_kb<64, 2, BF16OUT, LIST, true>(a, num_runs, stream)
                    : launch_dkdv_kb<128, 2, BF16OUT, LIST, true>(a, num_runs, stream);
@@ -956,7 +971,7 @@ static hsap_status launch_dkdv(const BwdArgs& a, int d, int64_t num_runs, hipStr
   }
   if (one) return launch_dkdv_kb<128, 1, BF16OUT, LIST>(a, num_runs, stream);
   // (a 64-row sub-tile has to fit 32-bit byte offsets)
-  if (a.bn == 64 || blocks <= 4 * kComputeUnits || (int64_t)a.hq * d * 64 > INT32_MAX)
+  if (a.bn == 64 || (LIST && blocks <= 1024) || (int64_t)a.hq * d * 64 > INT32_MAX)
     return launch_dkdv_kb<128, 2, BF16OUT, LIST>(a, num_runs, stream);
   return launch_dkdv_kb<128, 4, BF16OUT, LIST>(a, num_runs, stream);
 }

@@ -12,7 +12,7 @@ pytestmark = pytest.mark.gpu
 CASES = [
     # N, hq, hkv, d, bm, bn, document lengths (repeated to fill N); key blocks of 32 in the call
     (2048, 8, 8, 128, 128, 128, [700]),     # 512: 32 keys per workgroup, four streams
-    (2048, 9, 9, 128, 128, 128, [700]),     # 576: 64 keys, two streams
+    (2048, 9, 9, 128, 128, 128, [700]),     # 576: the same over runs; 64 keys, two streams in the tile-list call
     (2048, 16, 16, 128, 256, 64, [333]),    # 1024, 64-key tiles
     (4096, 18, 9, 128, 64, 128, [97, 5]),   # 1152: 128 keys, 64-row q-tiles, two query heads per K/V head
     (2048, 18, 18, 128, 64, 64, [2048]),    # 1152, 64-key tiles
@@ -95,6 +95,45 @@ def test_backward_unaligned_outputs(case):
     ex.close()
     for a, b in zip(got[0], got[1]):
         assert torch.equal(a, b)
+
+
+def _lists(c):
+    """Device inputs of a one-chunk case, its lists by k-tile and by q-tile, and a descriptor."""
+    from paper_2606_30460_amd import _lib as L
+    s = L.shard_desc(c.N, 1, "contiguous", 0, c.bm, c.bn)
+    desc = L.attn_desc(s, c.hq, c.hkv, c.d, c.d ** -0.5)
+    dev = torch.device("cuda")
+    q, k, v, d_o = (to_sharded(s, x.to(dev)).contiguous() for x in (c.q, c.k, c.v, c.do))
+    doc_start = torch.empty(c.N, dtype=torch.int32, device=dev)
+    L.doc_start(torch.from_numpy(c.cu).to(dev), c.N, doc_start)
+    tiles = L.plan(c.cu, s)["tiles"]
+    lists = [[torch.from_numpy(np.ascontiguousarray(x)).to(dev) for x in L.plan_runs(s, tiles, m, 0)[:2]]
+             for m in (L.MAJOR_K, L.MAJOR_Q_ALL)]
+    return desc, q, k, v, d_o, doc_start, lists
+
+
+@pytest.mark.parametrize("case", [(2048, 18, 18, 128, 128, 128, [700]), (2048, 36, 18, 64, 64, 64, [700, 31]),
+                                  (2048, 16, 16, 128, 64, 64, [2048])])
+def test_bits_do_not_depend_on_how_lists_are_cut(case):
+    # the same runs in one call and in five: the same bits (the workgroup's shape follows from the descriptor)
+    from paper_2606_30460_amd import _lib as L
+    c = _case(*case)
+    desc, q, k, v, d_o, doc_start, ((tk, rk), (ta, ra)) = _lists(c)
+    lse = torch.full((c.hq, c.N), 6.0, device="cuda")
+    delta = torch.randn(c.hq, c.N, generator=torch.Generator("cuda").manual_seed(3), device="cuda")
+    got = []
+    for pieces in (1, 5):
+        for fp32 in (False, True):
+            t = torch.float32 if fp32 else torch.bfloat16
+            out = [torch.zeros(x.shape, dtype=t, device="cuda") for x in (q, k, v)]
+            for i in range(pieces):
+                cut = lambda r: r[len(r) * i // pieces:len(r) * (i + 1) // pieces].contiguous().reshape(-1)
+                fn = L.partial_attn_bwd_runs if fp32 else L.attn_bwd_bf16
+                fn(desc, q, k, v, d_o, lse, delta, doc_start, tk.reshape(-1), cut(rk), ta.reshape(-1), cut(ra), *out)
+            got.append(out)
+    for a, b in ((got[0], got[2]), (got[1], got[3])):
+        for x, y in zip(a, b):
+            assert torch.equal(x, y), (case, x.dtype)
 
 
 @pytest.mark.parametrize("d", [64, 128])
