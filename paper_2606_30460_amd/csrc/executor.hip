@@ -428,6 +428,7 @@ hsap_status hsap_executor_merge(hsap_executor* ex, void* o_out, float* lse_out, 
   if (!ex) HSAP_FAIL(HSAP_ERR_INVALID_ARG, "NULL executor");
   if (!ex->planned) HSAP_FAIL(HSAP_ERR_INVALID_ARG, "executor has no plan");
   if (!o_out || !lse_out) HSAP_FAIL(HSAP_ERR_INVALID_ARG, "NULL pointer argument");
+  if (ex->merged_tiles.empty()) return HSAP_OK;  // every q-tile was written final; there may be no partial buffers
   const int32_t parts = ex->info.num_parts;
   const size_t rows = (size_t)ex->geom.n * ex->desc.heads_q;
   const float* o_ptrs[HSAP_MAX_MERGE_PARTS];
@@ -436,7 +437,6 @@ hsap_status hsap_executor_merge(hsap_executor* ex, void* o_out, float* lse_out, 
     o_ptrs[p] = (const float*)ex->o_part.p + (size_t)p * rows * ex->desc.head_dim;
     l_ptrs[p] = (const float*)ex->lse_part.p + (size_t)p * rows;
   }
-  if (ex->info.final_q_tiles == ex->nq) return HSAP_OK;  // every q-tile was written final
   return lse_merge(parts, o_ptrs, l_ptrs, ex->geom.n, ex->desc.heads_q, ex->desc.head_dim, o_out, lse_out,
                    ex->d_merged_tiles, (int32_t)ex->merged_tiles.size(), ex->desc.shard.block_m,
                    (hipStream_t)hip_stream);
