@@ -201,11 +201,26 @@ int32_t hsap_split_length(const hsap_shard_desc* shard, int64_t num_tiles, int32
                           int32_t resident_workgroups);
 
 /*
+ * hsap_fwd_split_length -- the max_run_tiles under which the bf16 partial
+ * forward of `desc` over one plan, with its merge, should take least time
+ * (host).  Candidates: no split (0) and pieces of a half, a third or a quarter
+ * of a chunk's k-tiles, at least 4 tiles and the average work per resident
+ * workgroup; the choice goes by an estimate from the runs' lengths, the key
+ * streams of the kernel and the partials to merge.
+ *   tiles, num_tiles  the list hsap_plan returned for desc->shard.
+ *   resident_workgroups  hsap_fwd_resident_workgroups of `desc`.
+ * Returns -1 for invalid arguments.  Not in the paper (scheduling of this
+ * library's kernels).
+ */
+int32_t hsap_fwd_split_length(const hsap_attn_desc* desc, const hsap_tile* tiles, int64_t num_tiles,
+                              int32_t resident_workgroups);
+
+/*
  * hsap_fwd_resident_workgroups -- workgroups of the bf16 partial forward that
  * fit on the current device at once for the shapes in `desc`: the HIP
  * runtime's occupancy of the kernel hsap_partial_attn_fwd_runs dispatches for
  * (head_dim, BM, BN) (its registers, LDS and workgroup size), times the
- * device's compute units -- the resident_workgroups of hsap_split_length.
+ * device's compute units -- the resident_workgroups of the two above.
  * Not in the paper (scheduling of this library's kernels).
  *   out  host int32, written (0 on failure).
  * Returns HSAP_ERR_UNSUPPORTED for shapes without a forward kernel and
@@ -738,11 +753,9 @@ typedef struct {
  * also those of hsap_partial_attn_bwd_runs, checked here: HSAP_ERR_UNSUPPORTED
  * before anything is allocated).
  *   options        HSAP_EXEC_* bits.
- *   max_run_tiles  q-major split: -1 picks hsap_split_length per plan from
+ *   max_run_tiles  q-major split: -1 picks hsap_fwd_split_length per plan from
  *                  hsap_fwd_resident_workgroups of the device current at
- *                  creation, but none (hsap_exec_info.split_length 0) unless the plan's
- *                  longest run exceeds four times the average work per resident
- *                  workgroup, 0 never splits, > 0 is used as given.  A plan whose split would need more than
+ *                  creation, 0 never splits, > 0 is used as given.  A plan whose split would need more than
  *                  HSAP_MAX_MERGE_PARTS partials is planned without split.
  *   out            receives the executor; NULL on failure.
  * Returns HSAP_ERR_HIP when device or pinned memory cannot be allocated.

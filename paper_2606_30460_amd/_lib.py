@@ -34,7 +34,7 @@ MAX_MERGE_PARTS = 64
 
 # Every symbol include/hsap.h declares.
 EXPORTED = (
-    "hsap_status_string", "hsap_last_error", "hsap_plan", "hsap_plan_runs", "hsap_split_length",
+    "hsap_status_string", "hsap_last_error", "hsap_plan", "hsap_plan_runs", "hsap_split_length", "hsap_fwd_split_length",
     "hsap_fwd_resident_workgroups", "hsap_load_matrix",
     "hsap_balance", "hsap_emit_forward", "hsap_emit_backward", "hsap_doc_start",
     "hsap_shard_gather", "hsap_partial_attn_fwd", "hsap_partial_attn_bwd", "hsap_partial_attn_fwd_runs", "hsap_attn_fwd_fused", "hsap_quantize_fp8", "hsap_quantize_fp8_noalloc",
@@ -97,6 +97,7 @@ _SIG = {
     "hsap_plan": (ctypes.c_int, [_P, _I32, _P, _P, _I64, _P, _P, _P]),
     "hsap_plan_runs": (ctypes.c_int, [_P, _P, _I64, _I32, _I32, _P, _P, _I64, _P, _P]),
     "hsap_split_length": (ctypes.c_int32, [_P, _I64, _I32, _I32]),
+    "hsap_fwd_split_length": (ctypes.c_int32, [_P, _P, _I64, _I32]),
     "hsap_fwd_resident_workgroups": (ctypes.c_int, [_P, _P]),
     "hsap_load_matrix": (ctypes.c_int, [_P, _I32, _P, _P, _P]),
     "hsap_balance": (ctypes.c_int, [_I32, _P, _P, _P]),
@@ -275,6 +276,15 @@ def plan_runs(shard: ShardDesc, tiles: np.ndarray, major: int, max_run_tiles: in
 def split_length(shard: ShardDesc, num_tiles: int, heads_q: int, resident_workgroups: int) -> int:
     """hsap_split_length: max_run_tiles for hsap_plan_runs (0 = no split)."""
     v = lib().hsap_split_length(ctypes.byref(shard), int(num_tiles), int(heads_q), int(resident_workgroups))
+    if v < 0:
+        raise HsapError(HSAP_ERR_INVALID_ARG, lib().hsap_last_error().decode())
+    return v
+
+
+def fwd_split_length(desc: AttnDesc, tiles: np.ndarray, resident_workgroups: int) -> int:
+    """hsap_fwd_split_length: max_run_tiles for hsap_plan_runs (0 = no split) for this plan's forward."""
+    tiles = np.ascontiguousarray(tiles, dtype=np.int32)
+    v = lib().hsap_fwd_split_length(ctypes.byref(desc), _ptr(tiles), len(tiles), int(resident_workgroups))
     if v < 0:
         raise HsapError(HSAP_ERR_INVALID_ARG, lib().hsap_last_error().decode())
     return v

@@ -37,7 +37,7 @@ from .shard_attention import _resident_workgroups
 class AllShards:
     """Plan and run all P shards of one packed sequence under the ring or the balanced schedule.
 
-    ``max_run_tiles``: split length of each shard's q-major runs (None: hsap_split_length
+    ``max_run_tiles``: split length of each shard's q-major runs (None: hsap_fwd_split_length
     for that shard, as a one-shard run picks it; 0: no split).
     """
 
@@ -79,7 +79,7 @@ class AllShards:
             tiles = L.plan(self.cu_host, shard)["tiles"]
             split = self.max_run_tiles
             if split is None:
-                split = L.split_length(shard, len(tiles), self.hq, resident)
+                split = L.fwd_split_length(self.descs[-1], tiles, resident)
             sorted_tiles, runs, _ = L.plan_runs(shard, tiles, L.MAJOR_Q, split)
             # partial slots renumbered densely, in increasing slot order (the merge order)
             present = sorted(set(runs[:, 0].tolist()))

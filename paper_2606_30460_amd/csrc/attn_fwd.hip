@@ -37,10 +37,6 @@ namespace hsap {
 // is ignored by untyped loads, but a zero format makes them return zeros).
 constexpr int kBufferWord3 = 0x00020000;
 
-// The direct-to-LDS kernel packs a tile descriptor as k_tile | chunk << 23 | kind << 31.
-constexpr int kMaxDlChunks = 256;
-constexpr int64_t kMaxDlKTiles = int64_t(1) << 23;
-
 struct FwdArgs {
   const __bf16* q;
   const __bf16* k;
@@ -850,7 +846,7 @@ template <int D, int BN, int WAVES, bool FUSED, bool FP8 = false>
 static hsap_status launch_dl(const FwdArgs& a, int64_t num_runs, hipStream_t stream) {
   if constexpr (WAVES < 8 && !FP8) {
     const int ks = FUSED ? key_streams(D, 32 * WAVES, a.geom.n / (32 * WAVES) * a.hq, a.geom.Ns)
-                         : fwd_key_streams(D, 32 * WAVES, a.hq, a.geom);
+                         : fwd_key_streams(D, 32 * WAVES, BN, a.hq, a.geom);
     if constexpr (D == 64 && WAVES == 2)
       if (ks == 4) return launch_dl_ks<D, BN, WAVES, FUSED, FP8, 4>(a, num_runs, stream);
     if (ks >= 2) return launch_dl_ks<D, BN, WAVES, FUSED, FP8, 2>(a, num_runs, stream);
@@ -917,7 +913,7 @@ static hsap_status forward(const hsap_attn_desc* desc, const void* q, const void
   a.scale_log2 = desc->softmax_scale * 1.44269504088896340736f;
   // the direct-to-LDS kernel's packed tile descriptors hold chunks below 256 and k-tiles below 2^23
   // (else, and for fp8 scores with 64-row q-tiles, the register-staged kernel)
-  const bool packed = geom.P <= kMaxDlChunks && geom.n / bn < kMaxDlKTiles;
+  const bool packed = dl_packed(geom, bn);
   if constexpr (FP8) {
     if ((uintptr_t)q & 15 || (uintptr_t)k & 15) HSAP_FAIL(HSAP_ERR_INVALID_ARG, "fp8 q and k must be 16-byte aligned");
     if (packed && bm == 256)
@@ -968,11 +964,11 @@ int fwd_resident_per_cu(const hsap_attn_desc* desc) {
   if (check_attn(desc, &geom) != HSAP_OK) return 0;
   const int bm = desc->shard.block_m, bn = desc->shard.block_n, d = desc->head_dim;
   if (bn != 64 && bn != 128) return 0;
-  const bool packed = geom.P <= kMaxDlChunks && geom.n / bn < kMaxDlKTiles;
+  const bool packed = dl_packed(geom, bn);
   if (packed && d == 128 && bm == 256)
     return bn == 128 ? blocks_per_cu(attn_fwd_dl_kernel<128, 128, 8, false>, 512)
                      : blocks_per_cu(attn_fwd_dl_kernel<128, 64, 8, false>, 512);
-  const int ks = packed ? fwd_key_streams(d, bm, desc->heads_q, geom) : 1;
+  const int ks = fwd_key_streams(d, bm, bn, desc->heads_q, geom);
   if (d == 64 && bm == 64 && ks == 4)
     return bn == 128 ? blocks_per_cu(attn_fwd_dl_kernel<64, 128, 2, false, false, false, 4>, 512)
                      : blocks_per_cu(attn_fwd_dl_kernel<64, 64, 2, false, false, false, 4>, 512);

@@ -235,25 +235,8 @@ hsap_status hsap_executor_plan(hsap_executor* ex, const int32_t* cu_seqlens, int
 
   // 2. q-major runs, split as configured; slots renumbered densely
   int32_t split = ex->max_run_tiles;
-  if (split < 0) split = hsap_split_length(&sd, T, ex->desc.heads_q, ex->resident_workgroups);
+  if (split < 0) split = hsap_fwd_split_length(&ex->desc, ex->tiles.data(), T, ex->resident_workgroups);
   if (split < 0) return HSAP_ERR_INVALID_ARG;
-  // The planner's split balances runs whose length could exceed the average work of a resident workgroup;
-  // pieces cost a prologue each, fp32 partials and the merge, so a split has to shorten the longest
-  // run there is by much: it is left out unless that run holds more than four times the average.
-  // Forward + merge with and without it: 32768 tokens, runs of up to 11 tiles for an average of 5.4: 48.1 and
-  // 38.8 us; 32 tiles for 14.2: 50.9 and 44.4 us; 8 tiles for 0.1 (one head): 18.2 and 20.2 us; 9 tiles for 2.3
-  // (2048 tokens x 4 heads of 64, one chunk): 12.6 and 9.8 us.  Of 21 random forwards of 20..115 us whose split
-  // the line drops, two lost 10 % (31 tiles for 9.5: 43.8 -> 48.8 us; 8 for 3.6 at 256-row q-tiles: 41.0 -> 45.5 us)
-  // and four 1..5 %, three stayed, twelve gained 2..36 %.
-  if (ex->max_run_tiles < 0 && split > 0) {
-    int64_t longest = 0, len = 0;  // the tiles are in (ring step, q-tile, k-tile) order
-    for (int64_t i = 0; i < T; ++i) {
-      const hsap_tile &t = ex->tiles[(size_t)i], &u = ex->tiles[(size_t)std::max<int64_t>(i - 1, 0)];
-      len = i > 0 && t.chunk == u.chunk && t.q_tile == u.q_tile ? len + 1 : 1;
-      longest = std::max(longest, len);
-    }
-    if (longest * ex->resident_workgroups <= 4 * T * ex->desc.heads_q) split = 0;
-  }
   int64_t RQ = 0;
   int32_t slots = 0;
   st = runs_for(ex, HSAP_MAJOR_Q, split, ex->sorted_q, ex->runs_q, &RQ, &slots);

@@ -91,9 +91,14 @@ inline int key_streams(int head_dim, int block_m, int64_t items, int64_t keys) {
   return items <= (head_dim == 128 && block_m == 128 ? 3 * kComputeUnits / 4 : kComputeUnits) ? 2 : 1;
 }
 
+// The direct-to-LDS forward packs a tile descriptor as k_tile | chunk << 23 | kind << 31.
+constexpr int kMaxDlChunks = 256;
+constexpr int64_t kMaxDlKTiles = int64_t(1) << 23;
+inline bool dl_packed(const Geom& g, int block_n) { return g.P <= kMaxDlChunks && g.n / block_n < kMaxDlKTiles; }
+
 // The same for the partial forward, whose runs each cover one chunk.
-inline int fwd_key_streams(int head_dim, int block_m, int heads_q, const Geom& g) {
-  return key_streams(head_dim, block_m, g.n / block_m * heads_q * g.P, g.ns);
+inline int fwd_key_streams(int head_dim, int block_m, int block_n, int heads_q, const Geom& g) {
+  return dl_packed(g, block_n) ? key_streams(head_dim, block_m, g.n / block_m * heads_q * g.P, g.ns) : 1;
 }
 
 #if defined(__HIPCC__)

@@ -17,6 +17,7 @@
 //   * otherwise its pair count is summed per document segment of its rows as
 //     two arithmetic series (rows before the k-tile's end, rows after it).
 #include <algorithm>
+#include <cmath>
 #include <cstdarg>
 #include <cstring>
 #include <numeric>
@@ -25,6 +26,117 @@
 #include "hsap_internal.h"
 
 namespace hsap {
+
+// The time of the partial forward and its merge over one chunk's runs, cut or not, in us (up to a constant):
+//   chain  the longest workgroup's 64-key steps or, beyond one workgroup per resident slot, those of the two that
+//          share the last slot
+//   work   the wave-steps of all runs over the chip's SIMDs, and a prologue and epilogue per workgroup
+//   merge  a launch, a term per part (its loop over them is serial), and the busy parts' rows written and read
+// Chain and work overlap in part: sqrt(chain^2 + work^2).  The constants were fitted over 16000 forwards of 7000
+// random plans (both head_dims, all tile shapes, 5..900 us; uncut and in two, three and four pieces a chunk), whose
+// times they meet within 5 % in the median.  The choice is within 0.4 % of the best of the four in the geometric mean,
+// 1 % of the plans lose over 10 % by it; always cutting into quarters as soon as a run can exceed the average lost
+// 4 %, and cutting only runs of over four times the average 4 % with single plans at half the speed.
+class SplitCost {
+ public:
+  SplitCost(const hsap_attn_desc& d, const Geom& g, int32_t resident)
+      : g_(g), nq_(g.n / d.shard.block_m), resident_(resident), heads_(d.heads_q), waves_(d.shard.block_m / 32),
+        subs_(d.shard.block_n / 64), streams_(fwd_key_streams(d.head_dim, d.shard.block_m, d.shard.block_n, d.heads_q, g)) {
+    // head_dim 64 and 128, one wave of a workgroup per SIMD and two (key streams, 256-row q-tiles)
+    const bool shared = waves_ * streams_ > 4;
+    c_ = d.head_dim == 64 ? (shared ? Constants{1.0, 1.12, 0.40, 3.45} : Constants{0.0, 0.80, 0.46, 1.0})
+         : waves_ == 8    ? Constants{6.9, 1.78, 0.71, 2.57}
+         : shared         ? Constants{6.9, 1.28, 0.81, 4.3}
+                          : Constants{4.3, 0.92, 0.79, 2.4};
+    if (waves_ == 2) c_.wave_step *= 1.34;
+    row_bytes_ = 4.0 * d.shard.block_m * d.heads_q * d.head_dim;
+    nk_ = g.ns / d.shard.block_n;
+  }
+
+  // The q-major runs of a planner's list: consecutive tiles of one (chunk, q-tile).
+  bool add_runs(const hsap_tile* t, int64_t n) {
+    tiles_ = n;
+    for (int64_t i = 0; i < n; ++i) {
+      if (i == 0 || t[i].chunk != t[i - 1].chunk || t[i].q_tile != t[i - 1].q_tile) {
+        if (t[i].chunk < 0 || t[i].chunk >= g_.P || t[i].q_tile < 0 || t[i].q_tile >= nq_) return false;
+        runs_.push_back({t[i].chunk, t[i].q_tile, 0});
+      }
+      longest_ = std::max(longest_, ++runs_.back().count);
+    }
+    return true;
+  }
+
+  // 0 (uncut) or the piece length of least time among a half, a third and a quarter of a chunk's k-tiles, none
+  // below 4 tiles and the average load per resident workgroup.
+  int32_t best() const {
+    const int64_t avg = (tiles_ * heads_ + resident_ - 1) / resident_;
+    int32_t len = 0;
+    if (longest_ <= std::max<int64_t>(avg, 4)) return len;
+    double least = time(longest_);
+    for (int64_t pieces = 2; pieces <= 4; ++pieces) {
+      const int64_t l = std::max<int64_t>({avg, 4, (nk_ + pieces - 1) / pieces});
+      if (l >= longest_) continue;
+      const double t = time((int32_t)l);
+      if (t < least) {
+        least = t;
+        len = (int32_t)l;
+      }
+    }
+    return len;
+  }
+
+ private:
+  struct Run {
+    int32_t chunk, q_tile, count;
+  };
+  struct Constants {
+    double chain, step;       // us of a chain: its start and end, and each 64-key step
+    double wave_step, wave;   // us of a SIMD's work: a wave's step, a wave's start and end
+  };
+
+  double time(int32_t len) const {
+    std::vector<int32_t> lengths((size_t)longest_ + 1, 0);   // pieces of each length
+    std::vector<int32_t> pieces((size_t)nq_, 0);             // of each q-tile
+    std::vector<int32_t> slots((size_t)g_.P, 0);             // a chunk's slots: the most pieces a run of it has
+    for (const Run& r : runs_) {
+      const int32_t p = (r.count + len - 1) / len, a = r.count / p, longer = r.count % p;
+      lengths[(size_t)a] += p - longer;
+      if (longer) lengths[(size_t)a + 1] += longer;
+      pieces[(size_t)r.q_tile] += p;
+      slots[(size_t)r.chunk] = std::max(slots[(size_t)r.chunk], p);
+    }
+    int64_t merged = 0, busy = 0, parts = 0;
+    for (const int32_t p : pieces) {
+      merged += p > 1;
+      busy += p > 1 ? p : 0;
+    }
+    for (const int32_t p : slots) parts += p;
+    if (len < longest_ && parts > HSAP_MAX_MERGE_PARTS) return HUGE_VAL;  // more than one merge takes
+    // the longest piece, and the lengths around the last resident workgroup, longest first
+    int64_t seen = 0, first = 0, last = 0, next = 0;
+    for (int64_t l = longest_; l > 0 && !next; --l) {
+      if (!lengths[(size_t)l]) continue;
+      if (!first) first = l;
+      const int64_t until = seen + (int64_t)lengths[(size_t)l] * heads_;
+      if (seen < resident_ && until >= resident_) last = l;
+      if (until > resident_) next = l;
+      seen = until;
+    }
+    const double chain = c_.chain + c_.step * std::max(first, next ? last + next : 0) * subs_ / streams_;
+    // (every slot has a run for every merged q-tile: the empty ones write LSE = -inf)
+    const double simds = 4.0 * kComputeUnits, workgroups = (double)(merged * parts + nq_ - merged) * heads_;
+    const double work = (c_.wave_step * tiles_ * subs_ * heads_ + c_.wave * workgroups) * waves_ / simds;
+    const double merge = merged ? 4.2 + 0.63 * parts + 0.21e-6 * row_bytes_ * busy : 0.0;
+    return std::sqrt(chain * chain + work * work) + merge;
+  }
+
+  Geom g_;
+  int64_t nq_, nk_, resident_, heads_, tiles_ = 0;
+  int32_t waves_, subs_, streams_, longest_ = 0;
+  double row_bytes_;
+  Constants c_;
+  std::vector<Run> runs_;
+};
 
 static thread_local std::string g_last_error;
 
@@ -456,6 +568,23 @@ int32_t hsap_split_length(const hsap_shard_desc* shard, int64_t num_tiles, int32
   if (nk <= avg) return 0;  // no run can exceed the average load
   const int64_t len = std::max<int64_t>({avg, 4, (nk + 3) / 4});
   return len >= nk ? 0 : (int32_t)len;
+}
+
+int32_t hsap_fwd_split_length(const hsap_attn_desc* desc, const hsap_tile* tiles, int64_t num_tiles,
+                              int32_t resident_workgroups) {
+  clear_error();
+  Geom g;
+  if (check_attn(desc, &g) != HSAP_OK) return -1;
+  if (num_tiles < 0 || (num_tiles > 0 && !tiles) || resident_workgroups <= 0) {
+    set_error("bad tiles or resident_workgroups");
+    return -1;
+  }
+  SplitCost cost(*desc, g, resident_workgroups);
+  if (!cost.add_runs(tiles, num_tiles)) {
+    set_error("tile outside the shard");
+    return -1;
+  }
+  return cost.best();
 }
 
 }  // extern "C"

@@ -4,7 +4,7 @@ This is call sequencing and buffer allocation only, one entry point at a
 time (the library's hsap_executor runs the same sequence natively, one call
 per stage); every step of the path runs inside the library:
 
-  plan      hsap_plan (host C++) -> hsap_split_length / hsap_plan_runs ->
+  plan      hsap_plan (host C++) -> hsap_fwd_split_length / hsap_plan_runs ->
             upload of the lists, hsap_doc_start (device)
   forward   hsap_partial_attn_fwd over the runs (one launch for every chunk,
             or one launch per ring step), then hsap_lse_merge of every slot
@@ -42,9 +42,7 @@ class ShardAttention:
 
     ``max_run_tiles``: longest q-major run before it is split into pieces
     (split-K over partial slots); None picks it from the plan and the number
-    of resident workgroups (hsap_split_length, and no split unless the longest
-    run exceeds four times the average per workgroup, as the executor
-    decides), 0 disables splitting.
+    of resident workgroups (hsap_fwd_split_length), 0 disables splitting.
     """
 
     def __init__(self, cu_seqlens, total_tokens: int, sp_degree: int, layout, shard_id: int, heads_q: int,
@@ -65,14 +63,7 @@ class ShardAttention:
     def _split(self, tiles: np.ndarray) -> int:
         if self.max_run_tiles is not None:
             return int(self.max_run_tiles)
-        resident = _resident_workgroups(self.device, self.desc)
-        split = L.split_length(self.shard, len(tiles), self.hq, resident)
-        if split > 0:  # as the executor decides: no split unless the longest run is well above the average
-            runs = tiles[:, 0].astype(np.int64) << 32 | tiles[:, 1]
-            longest = int(np.unique(runs, return_counts=True)[1].max())
-            if longest * resident <= 4 * len(tiles) * self.hq:
-                split = 0
-        return split
+        return L.fwd_split_length(self.desc, tiles, _resident_workgroups(self.device, self.desc))
 
     # ------------------------------------------------------------------ plan
     def plan(self, backward: bool = False) -> Dict:

@@ -65,6 +65,13 @@ int main(int argc, char** argv) {
       }
       if (covered != nt) { printf("runs cover %lld of %lld (major %d)\n", (long long)covered, (long long)nt, major); return 1; }
     }
+    hsap_attn_desc ad{};
+    ad.shard = sd;
+    ad.heads_q = (int32_t)U(1, 64);
+    ad.heads_kv = 1;
+    ad.head_dim = U(0, 1) ? 64 : 128;
+    ad.softmax_scale = 0.125f;
+    (void)hsap_fwd_split_length(&ad, tiles.data(), nt, (int32_t)U(1, 1024));
     (void)hsap_split_length(&sd, nt, (int32_t)U(1, 64), (int32_t)U(1, 1024));
     std::vector<int64_t> lt((size_t)P * P), lp((size_t)P * P);
     st = hsap_load_matrix(cu.data(), nd, &sd, lt.data(), lp.data());

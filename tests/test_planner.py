@@ -157,6 +157,43 @@ def test_split_length():
         L.split_length(d, 10, 0, 512)
 
 
+@pytest.mark.parametrize("N,P,layout,hq,hd,bm,bn,lengths,resident,cut", [
+    # few long runs leave the chip idle: 85.2 us uncut, 51.0 us in quarters; 140 and 85 us; 77 and 53 us
+    (6528, 1, "contiguous", 3, 128, 128, 128, [5976] + [8] * 69, 256, True),
+    (46080, 6, "contiguous", 6, 128, 256, 64, [7000] * 6 + [4080], 256, True),
+    (46080, 12, "contiguous", 8, 128, 256, 64, [3000] * 15 + [1080], 256, True),
+    # pieces of five tiles would only add partials and a merge: 9.8 us uncut, 12.6 us cut
+    (2048, 1, "contiguous", 4, 64, 64, 64, [340] * 6 + [8], 256, False),
+    # many heads: every run is below the average work of a workgroup
+    (65536, 8, "zigzag", 16, 64, 128, 128, [65536], 768, False),
+    (4096, 2, "contiguous", 8, 128, 128, 128, [64] * 64, 512, False),
+])
+def test_fwd_split_length(N, P, layout, hq, hd, bm, bn, lengths, resident, cut):
+    s = L.shard_desc(N, P, layout, P - 1, bm, bn)
+    desc = L.attn_desc(s, hq, 1, hd, hd ** -0.5)
+    tiles = L.plan(np.concatenate([[0], np.cumsum(lengths)]).astype(np.int32), s)["tiles"]
+    longest = int(np.unique(tiles[:, :2], axis=0, return_counts=True)[1].max())
+    got = L.fwd_split_length(desc, tiles, resident)
+    assert (got > 0) == cut, got
+    if got:
+        avg, nk = -(-len(tiles) * hq // resident), N // P // bn
+        assert got in [max(4, avg, -(-nk // pieces)) for pieces in (2, 3, 4)] and got < longest
+
+
+def test_fwd_split_length_rejects():
+    s = L.shard_desc(4096, 2, "contiguous", 1, 128, 128)
+    desc = L.attn_desc(s, 2, 1, 128, 0.1)
+    tiles = L.plan(np.array([0, 4096], dtype=np.int32), s)["tiles"]
+    assert L.fwd_split_length(desc, tiles[:0], 256) == 0
+    for column, value in ((0, 2), (0, -1), (1, 16), (1, -1)):    # chunk, q_tile outside the shard
+        bad = tiles.copy()
+        bad[1, column] = value
+        with pytest.raises(L.HsapError):
+            L.fwd_split_length(desc, bad, 256)
+    with pytest.raises(L.HsapError):
+        L.fwd_split_length(desc, tiles, 0)
+
+
 # ---------------------------------------------------------------------------
 # block loads of every shard (hsap_load_matrix) and the Q-transfer rebalance (hsap_balance)
 # ---------------------------------------------------------------------------
