@@ -51,6 +51,67 @@ def test_backward_workgroup_shapes(case):
             assert err <= 2.0 ** -7, (case, key, err)
 
 
+# runs of more than 64 tiles, so the kernels load a second and a third window of descriptors, and the dK/dV kernel
+# starts over with the first at each query head of the group
+LONG = [
+    (8320, 1, 1, 64, 64, 64, [8320]),       # dK/dV 32 keys a workgroup; dQ four streams
+    (4288, 6, 3, 64, 64, 64, [4288]),       # 32 keys, two heads a group; two streams
+    (8320, 4, 2, 64, 64, 64, [8320]),       # the tile-list call 64 keys, the runs 32; one stream
+    (4288, 12, 6, 64, 64, 64, [4288]),      # 64 keys
+    (4288, 2, 1, 128, 64, 64, [4288]),      # head_dim 128: 32 keys; two streams
+    (4288, 12, 6, 128, 64, 64, [4288]),     # 64 keys; one stream
+    (8320, 2, 1, 128, 64, 128, [8320]),     # 128-key tiles, 32 keys
+    (8320, 4, 4, 128, 64, 128, [8320]),     # 128 keys
+]
+
+
+@pytest.mark.parametrize("case", LONG)
+def test_backward_descriptor_windows(case):
+    test_backward_workgroup_shapes(case)
+
+
+# several chunks and zigzag shards on both sides of the lines where the workgroups' keys (reachable 32-key blocks: 640
+# for 128-key tiles, 768 for 64-key tiles, 512 in a chunk for the tile-list call) and the dQ streams change
+CHUNKS = [
+    # N, P, layout, shard, hq, hkv, d, bm, bn, document lengths
+    (4096, 2, "zigzag", 1, 10, 5, 128, 128, 128, [4096]),       # 480 reachable, 80 q-tiles x heads
+    (4096, 2, "zigzag", 0, 14, 7, 128, 128, 128, [900, 33]),    # 896
+    (4096, 2, "contiguous", 1, 8, 8, 64, 64, 64, [2500, 7]),    # 1024, in a chunk 512; 256
+    (4096, 4, "contiguous", 1, 10, 10, 64, 128, 64, [4096]),    # 640
+    (6144, 3, "contiguous", 2, 4, 2, 128, 64, 64, [130, 3000]),     # 384; 128
+    (6144, 3, "contiguous", 2, 6, 6, 128, 256, 128, [130, 3000]),   # 1152
+]
+
+
+@pytest.mark.parametrize("case", CHUNKS)
+def test_backward_workgroup_shapes_of_chunks(case):
+    # the bar of test_backward_workgroup_shapes
+    N, P, layout, shard, hq, hkv, d, bm, bn, docs = case
+    c = _case(N, hq, hkv, d, bm, bn, docs)
+    c = Case(c.cu, N, P, layout, shard, hq, hkv, d, bm, bn, seed=2, backward=True)
+    ref = c.run_oracle()
+    for got in (c.run_executor(), c.run_tile_list()):
+        rep = compare_backward(got, ref)
+        assert max(rep.values()) <= 2.0 ** -7, (case, rep)
+        for key in ("dk", "dv"):
+            err = np.linalg.norm(got[key] - ref[key]) / np.linalg.norm(ref[key])
+            assert err <= 2.0 ** -7, (case, key, err)
+
+
+@pytest.mark.parametrize("d,bm,bn", [(64, 64, 64), (128, 128, 128)])
+def test_many_empty_documents_in_a_wave(d, bm, bn):
+    # repeated cu_seqlens entries are documents of no tokens: a hundred among one wave's 32 queries (inside
+    # rows 64..95, and at the first row of 192..223), more boundaries than the kernels' 64-entry window holds
+    cu = [0, 40] + [70] * 100 + [75, 128] + [192] * 100 + [200] + [200] * 70 + [256]
+    c = Case(np.asarray(cu, dtype=np.int32), 256, 1, "contiguous", 0, 2, 1, d, bm, bn, seed=5, backward=True)
+    got, ref = c.run_executor(), c.run_oracle()
+    rep = compare_backward(got, ref)
+    assert max(rep.values()) <= 2.0 ** -7, rep
+    for form in ("", "_fused"):
+        for key, tol in (("o", 2.0 ** -7), ("lse", 1e-5)):
+            assert np.linalg.norm(got[key + form] - ref[key]) / np.linalg.norm(ref[key]) <= tol, key + form
+
+
 @pytest.mark.parametrize("case", CASES[:7])
 def test_dk_keeps_p_in_32_bits(case):
     # dS = P (dP - delta) from P in fp32: bf16 roundings (to nearest) leave the component of dK along the

@@ -10,6 +10,7 @@ pytestmark = pytest.mark.gpu
 CASES = [
     # N, P, layout, shard, hq, hkv, d, bm, bn, document lengths (repeated to fill N)
     (8320, 1, "contiguous", 0, 2, 1, 64, 64, 64, [8320]),       # runs of up to 130 tiles, odd and even
+    (8320, 1, "contiguous", 0, 1, 1, 64, 64, 64, [8320]),       # the same over four key streams
     (8320, 1, "contiguous", 0, 1, 1, 64, 128, 64, [8320]),
     (16640, 2, "contiguous", 1, 1, 1, 64, 128, 128, [16640]),   # 65 tiles per chunk
     (8320, 1, "contiguous", 0, 1, 1, 128, 64, 64, [8320]),

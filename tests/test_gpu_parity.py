@@ -13,7 +13,7 @@ import numpy as np
 import pytest
 import torch
 
-from _harness import Case, compare_backward, compare_forward, max_abs, rel_max
+from _harness import Case, compare_backward, compare_forward, compare_tile_list, max_abs, rel_max
 from paper_2606_30460_amd.shard_attention import to_sharded
 from workloads import make_workload
 
@@ -79,6 +79,19 @@ def test_forward_many_chunks():
         _say("forward many chunks, shard", r)
         c = Case(cu, N, P, "contiguous", r, 2, 2, 128, 128, 128, seed=r)
         compare_forward(c.run_gpu(), c.run_oracle())
+
+
+@pytest.mark.parametrize("d,bm,bn", [(128, 128, 128), (128, 128, 64), (128, 64, 128), (128, 64, 64),
+                                     (64, 128, 128), (64, 128, 64), (64, 64, 128), (64, 64, 64)])
+def test_forward_many_chunks_shapes(d, bm, bn):
+    # every shape of the register-staged kernel, which runs beyond 256 chunks: runs, fused, tile lists
+    N, P, r = 260 * 128, 260, 200
+    cu = _rand_cu(np.random.default_rng(261), N, 1000)
+    _say("forward many chunks", d, bm, bn)
+    c = Case(cu, N, P, "contiguous", r, 2, 1, d, bm, bn, seed=r)
+    ref = c.run_oracle()
+    compare_forward(c.run_gpu(max_run_tiles=0), ref)
+    compare_tile_list(c.run_tile_list(), ref)
 
 
 @pytest.mark.parametrize("split", [0, 1, 3])
