@@ -820,7 +820,10 @@ hsap_status hsap_executor_merge(hsap_executor* ex, void* o_out, float* lse_out, 
  * MAJOR_Q_ALL runs, which write every other row of those chunks.  The dQ
  * kernel runs first and computes the preprocess (delta of
  * hsap_attn_bwd_preprocess) for its rows from o and d_o, and their document
- * starts from cu_seqlens; the dK/dV kernel reads both.
+ * starts from cu_seqlens; the dK/dV kernel reads both.  How many keys a dK/dV
+ * workgroup takes (and so the order of its sums) follows from the plan's run
+ * lengths here, where the entry points go by the descriptor: their gradients
+ * can differ in the rounding of those sums.
  *   q, k, v  as for the forward;  d_o, o  device bf16 [n, Hq, d] (o: the
  *            forward's output);  lse  device fp32 [Hq, n] (the forward's).
  *   dq       device bf16 [n, Hq, d].

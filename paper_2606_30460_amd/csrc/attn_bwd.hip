@@ -23,6 +23,8 @@
 // dQ kernel: one workgroup per (q-major run, query head), shaped like the
 // forward; it forms S and dP again for its own pairs (described below).
 //
+#include <algorithm>
+#include <cmath>
 #include <type_traits>
 
 #include "hsap_internal.h"
@@ -113,7 +115,8 @@ constexpr int kMaxListQTiles = 2048;
 // ---------------------------------------------------------------------------
 // WIDE: Q rows of so many heads that 32 of them do not fit 32-bit byte offsets (the transfers take
 // 64-bit addresses per lane).
-template <int D, int KB, bool BF16OUT, bool LIST, bool WIDE = false>
+// P32: P handed over in fp32, otherwise in fp16.
+template <int D, int KB, bool BF16OUT, bool LIST, bool WIDE = false, bool P32 = KB < 4 || LIST>
 __global__ __launch_bounds__(512, D == 64 && KB == 2 ? 4 : 2) void attn_bwd_dkdv_kernel(BwdArgs a) {
   static_assert(!LIST || !BF16OUT, "the tile-list mode accumulates fp32");
   static_assert((D == 128 || D == 64) && (KB == 4 || KB == 2 || KB == 1), "shapes with a kernel");
@@ -133,13 +136,12 @@ __global__ __launch_bounds__(512, D == 64 && KB == 2 ? 4 : 2) void attn_bwd_dkdv
   constexpr int TILE = SUB * D;                                  // elements of one sub-tile
   constexpr int RING_BYTES = QS * RING * 2 * TILE * 2;
   // P per pair and 32-query block: lane l's 16 values as 16-byte pieces at [piece][l] (consecutive
-  // lanes at consecutive 16 bytes: no bank conflict).  KB = 4 over runs: fp16, two buffers (P of
-  // t + 1 is written while the dP wave reads P of t).  Else fp32, one buffer in the same room: in
-  // the three-slot ring, whose iterations have one barrier, a pair's S wave overwrites P of t once its
-  // dP wave has counted it as taken.  (fp32 for KB = 4 over runs costs 4 %: 131072-token step 13.96 ->
+  // lanes at consecutive 16 bytes: no bank conflict).  KB = 4 over the runs of more than 1024 key blocks: fp16,
+  // two buffers (P of t + 1 is written while the dP wave reads P of t).  Else fp32, one buffer in the same
+  // room: in the three-slot ring, whose iterations have one barrier, a pair's S wave overwrites P of t once its
+  // dP wave has counted it as taken.  (fp32 for KB = 4 over all runs costs 4 %: 131072-token step 13.96 ->
   // 14.53 ms; elsewhere fp16 would gain 1..6 %, layer 32k of head_dim 64 871 -> 820 us, but dS would be
   // formed from 11 bits of P.)
-  constexpr bool P32 = KB < 4 || LIST;
   constexpr int PIECES = 4 * QB * (P32 ? 4 : 2);  // of 64 x 16 bytes, the four pairs' P of one sub-tile
   constexpr int P_BYTES = PIECES * 64 * 16 * (P32 ? 1 : 2);
   constexpr int ACC_STRIDE = D + 8;
@@ -926,28 +928,34 @@ __global__ __launch_bounds__(64 * WAVES * KS, 2) void attn_bwd_dq_kernel(BwdArgs
     }
 }
 
-template <int D, int KB, bool BF16OUT, bool LIST, bool WIDE = false>
+template <int D, int KB, bool BF16OUT, bool LIST, bool WIDE = false, bool P32 = KB < 4 || LIST>
 static hsap_status launch_dkdv_kb(BwdArgs a, int64_t num_runs, hipStream_t stream) {
   a.parts = a.bn / (32 * KB);
   const int64_t blocks = num_runs * a.parts * a.hkv;
   if (blocks > INT32_MAX) HSAP_FAIL(HSAP_ERR_INVALID_ARG, "too many runs x heads");
-  hipLaunchKernelGGL((attn_bwd_dkdv_kernel<D, KB, BF16OUT, LIST, WIDE>), dim3((unsigned)blocks), dim3(512), 0, stream, a);
+  hipLaunchKernelGGL((attn_bwd_dkdv_kernel<D, KB, BF16OUT, LIST, WIDE, P32>), dim3((unsigned)blocks), dim3(512), 0, stream, a);
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) HSAP_FAIL(HSAP_ERR_HIP, "attn_bwd_dkdv launch: %s", hipGetErrorString(e));
   return HSAP_OK;
 }
 
-// k-tiles of the whole K/V that the shard's queries can reach under the causal mask (all their documents
-// being one): per sequence, the keys up to the shard's last row.
-static int64_t reachable_k_tiles(const Geom& g, int32_t shard, int32_t bn) {
-  const int64_t keys = (g.layout == HSAP_LAYOUT_CONTIGUOUS ? shard + 1 : 2 * g.P - shard) * g.m;
-  return g.B * ((keys + bn - 1) / bn);
+// Key blocks of 32, times K/V heads, that the shard's queries can reach under the causal mask (all their
+// documents being one): per sequence, the k-tiles up to the shard's last row.
+static int64_t reachable_key_blocks(const hsap_attn_desc& d, const Geom& g) {
+  const int64_t keys = (g.layout == HSAP_LAYOUT_CONTIGUOUS ? d.shard.shard_id + 1 : 2 * g.P - d.shard.shard_id) * g.m;
+  return g.B * ((keys + d.shard.block_n - 1) / d.shard.block_n) * (d.shard.block_n / 32) * d.heads_kv;
+}
+
+// Most key blocks of 32 a dK/dV workgroup can take.
+static int most_key_blocks(const hsap_attn_desc& d) {
+  // (a 64-row sub-tile has to fit 32-bit byte offsets)
+  return d.head_dim == 128 && d.shard.block_n == 128 && (int64_t)d.heads_q * d.head_dim * 64 <= INT32_MAX ? 4 : 2;
 }
 
 // Key blocks of 32 per dK/dV workgroup (one workgroup per CU is resident, at head_dim 64 two of 64 keys).
 // Fewer key blocks per workgroup give more, shorter workgroups at more staging traffic per product,
-// which pays while the grid leaves the chip idle.  The choice depends on the descriptor alone -- the key
-// blocks the shard can reach (tile-list call: those of its chunk) -- so that calls over the same tiles give
+// which pays while the grid leaves the chip idle.  In the entry points the choice depends on the descriptor alone --
+// the key blocks the shard can reach (tile-list call: those of its chunk) -- so that calls over the same tiles give
 // the same bits however their lists are cut and whichever other tiles share the call.  Over 600 random
 // backwards (dQ included; geometric mean of the gain against one wave per 32 keys at 64-key tiles, 128
 // keys per workgroup at 128-key tiles; in brackets the worst of them):
@@ -958,21 +966,73 @@ static int64_t reachable_k_tiles(const Geom& g, int32_t shard, int32_t bn) {
 // Tile-list calls at one causal document, head_dim 128 (us for 128 / 64 / 32 keys): 512 blocks 111.9 / 84.1 / 62.4,
 // 1024 blocks 115.4 / 98.9 / 120.2, 2048 blocks 152.3 / 194.2 / 247.3; head_dim 64 (64 / 32 keys): 512 blocks
 // 66.3 / 46.2, 1024 blocks 71.5 / 88.6.
+static int key_blocks(const hsap_attn_desc& d, int64_t blocks) {
+  return blocks <= (d.shard.block_n == 128 ? 640 : 768) ? 1 : most_key_blocks(d);
+}
+
+static int list_key_blocks(const hsap_attn_desc& d, int64_t blocks) {
+  return blocks <= 512 ? 1 : blocks <= 1024 ? 2 : most_key_blocks(d);
+}
+
+// Up to this many key blocks 128 keys per workgroup take P in fp32, as fewer keys do.
+constexpr int64_t kFp32Blocks = 1024;
+
+// The same for all k-major runs of a plan, whose lengths the executor has on the host: the choice of least estimated
+// time, sqrt(chain^2 + work^2), where the chain is that of the longest workgroup or, beyond one workgroup per slot, of
+// the two that share the last slot, and the work is per slot.  The descriptor's choice stands unless another saves
+// 0.5 us.  Fitted over 2500 random backwards (20..2000 us) run with every choice, and within 0.2 % of the best of them
+// in the geometric mean.  The whole backward's gain against one wave per 32 keys (64-key tiles) or 128 keys per
+// workgroup (128-key tiles), by the descriptor / by the plan (the worst of the latter): 128-key tiles 1.21 / 1.27
+// (0.96), 64-key tiles at head_dim 128 1.41 / 1.44 (0.93), at 64 1.50 / 1.56 (1.05).  What the descriptor does not show is
+// how few k-tiles of those in reach have tiles: 544 -> 312 us (716 tiles, 8 heads of 64 over one, 26880 tokens over 7).
+int plan_key_blocks(const hsap_attn_desc& d, const Geom& g, const hsap_run* runs, int64_t num_runs, int64_t num_tiles) {
+  struct Cost {
+    double step, wave, work, fixed;  // us: 32 rows of a chain; per slot a workgroup, and 32 rows; a constant
+  };
+  const int by_desc = key_blocks(d, reachable_key_blocks(d, g)), most = most_key_blocks(d);
+  const int64_t blocks = num_runs * (d.shard.block_n / 32) * d.heads_kv;
+  if (num_runs <= 0) return by_desc;
+  const double slices = (double)(d.heads_q / d.heads_kv) * d.shard.block_m / 32;  // 32-row slices per q-tile of a run
+  auto time = [&](int kb) {
+    const Cost c = d.head_dim == 64        ? (kb == 1 ? Cost{0.20, 2.23, 0.241, -0.27} : Cost{0.504, 0.0, 0.448, 0.0})
+                   : d.shard.block_n == 64 ? (kb == 1 ? Cost{0.325, 2.23, 0.494, -0.63} : Cost{0.605, 0.0, 0.814, 0.0})
+                   : kb == 1               ? Cost{0.271, 3.32, 0.381, -2.2}
+                   : kb == 2               ? Cost{0.543, 2.38, 0.579, -1.15}
+                   : blocks <= kFp32Blocks ? Cost{0.897, 0.0, 0.758, -0.44}
+                                           : Cost{0.74, 0.0, 0.696, 0.0};
+    const int64_t slots = kComputeUnits * (d.head_dim == 64 && kb == 2 ? 2 : 1);
+    const int64_t each = (int64_t)(d.shard.block_n / (32 * kb)) * d.heads_kv;  // workgroups per run (longest runs first)
+    int64_t chain = runs[0].count;
+    if (num_runs * each > slots) chain = std::max<int64_t>(chain, runs[(slots - 1) / each].count + runs[slots / each].count);
+    const double a = c.step * slices * chain;
+    const double b = (c.work * slices * num_tiles + c.wave * num_runs) * each / slots;
+    return std::sqrt(a * a + b * b) + c.fixed;
+  };
+  int best = by_desc;
+  double least = time(by_desc) - 0.5;
+  for (int kb = 1; kb <= most; kb *= 2) {
+    if (kb == by_desc) continue;
+    const double t = time(kb);
+    if (t < least) {
+      least = t;
+      best = kb;
+    }
+  }
+  return best;
+}
+
 template <bool BF16OUT, bool LIST = false>
-static hsap_status launch_dkdv(const BwdArgs& a, int d, int64_t num_runs, hipStream_t stream) {
-  const int64_t blocks = (LIST ? num_runs : reachable_k_tiles(a.geom, a.shard, a.bn)) * (a.bn / 32) * a.hkv;
-  const bool one = blocks <= (LIST ? 512 : a.bn == 128 ? 640 : 768);
+static hsap_status launch_dkdv(const BwdArgs& a, int d, int kb, int64_t blocks, int64_t num_runs, hipStream_t stream) {
   if ((int64_t)a.hq * d * 32 > INT32_MAX)
     return d == 64 ? launch_dkdv_kb<64, 2, BF16OUT, LIST, true>(a, num_runs, stream)
                    : launch_dkdv_kb<128, 2, BF16OUT, LIST, true>(a, num_runs, stream);
   if (d == 64) {
-    if (one) return launch_dkdv_kb<64, 1, BF16OUT, LIST>(a, num_runs, stream);
+    if (kb == 1) return launch_dkdv_kb<64, 1, BF16OUT, LIST>(a, num_runs, stream);
     return launch_dkdv_kb<64, 2, BF16OUT, LIST>(a, num_runs, stream);
   }
-  if (one) return launch_dkdv_kb<128, 1, BF16OUT, LIST>(a, num_runs, stream);
-  // (a 64-row sub-tile has to fit 32-bit byte offsets)
-  if (a.bn == 64 || (LIST && blocks <= 1024) || (int64_t)a.hq * d * 64 > INT32_MAX)
-    return launch_dkdv_kb<128, 2, BF16OUT, LIST>(a, num_runs, stream);
+  if (kb == 1) return launch_dkdv_kb<128, 1, BF16OUT, LIST>(a, num_runs, stream);
+  if (kb == 2) return launch_dkdv_kb<128, 2, BF16OUT, LIST>(a, num_runs, stream);
+  if (blocks <= kFp32Blocks) return launch_dkdv_kb<128, 4, BF16OUT, LIST, false, true>(a, num_runs, stream);
   return launch_dkdv_kb<128, 4, BF16OUT, LIST>(a, num_runs, stream);
 }
 
@@ -1004,8 +1064,8 @@ constexpr int64_t kMaxDqKTiles = int64_t(1) << 23;
 
 }  // namespace hsap
 
-// (head_dim, BM, BN) combinations with both backward kernels: the dK/dV kernel takes any BM that
-// is a multiple of 64 (64-row sub-tiles) and BN = 32 x waves; the dQ kernel BM = 32 x waves.
+// (head_dim, BM, BN) combinations with both backward kernels: the dK/dV kernel takes any BM that is a multiple
+// of 64 (its sub-tiles have 64 or 32 rows) and BN = 64 or, at head_dim 128, 128; the dQ kernel BM = 32 x waves.
 bool hsap::backward_supported(const hsap_attn_desc* desc) {
   const int bm = desc->shard.block_m, bn = desc->shard.block_n, d = desc->head_dim;
   const bool dkdv_ok = bm % 64 == 0 && ((d == 128 && (bn == 128 || bn == 64)) || (d == 64 && bn == 64));
@@ -1024,7 +1084,7 @@ static hsap_status backward(const hsap_attn_desc* desc, const void* q, const voi
                             const void* o, const float* lse, const float* delta, float* delta_out,
                             const int32_t* cu, int32_t num_docs, const int32_t* doc_start, const hsap_tile* tiles_k, const hsap_run* runs_k,
                             int64_t num_runs_k, const hsap_tile* tiles_q, const hsap_run* runs_q,
-                            int64_t num_runs_q, void* dq, void* dk, void* dv, hipStream_t s) {
+                            int64_t num_runs_q, void* dq, void* dk, void* dv, int kb, hipStream_t s) {
   Geom geom;
   hsap_status st = check_attn(desc, &geom);
   if (st != HSAP_OK) return st;
@@ -1103,7 +1163,9 @@ static hsap_status backward(const hsap_attn_desc* desc, const void* q, const voi
   if (num_runs_k > 0) {
     a.tiles = tiles_k;
     a.runs = runs_k;
-    st = launch_dkdv<BF16OUT>(a, d, num_runs_k, s);
+    // (kb: the executor's choice for its plan, whose runs these are)
+    const int64_t blocks = kb > 0 ? num_runs_k * (bn / 32) * desc->heads_kv : reachable_key_blocks(*desc, geom);
+    st = launch_dkdv<BF16OUT>(a, d, kb > 0 ? kb : key_blocks(*desc, blocks), blocks, num_runs_k, s);
     if (st != HSAP_OK) return st;
   }
   return HSAP_OK;
@@ -1174,7 +1236,8 @@ static hsap_status backward_tile_list(const hsap_attn_desc* desc, const void* q,
   else HSAP_DQ_CASE(64, 64, 2)
 #undef HSAP_DQ_CASE
   if (st != HSAP_OK) return st;
-  return launch_dkdv<false, true>(a, d, k_tiles, s);
+  const int64_t blocks = k_tiles * (bn / 32) * desc->heads_kv;
+  return launch_dkdv<false, true>(a, d, list_key_blocks(*desc, blocks), blocks, k_tiles, s);
 }
 
 }  // namespace hsap
@@ -1198,7 +1261,7 @@ extern "C" hsap_status hsap_partial_attn_bwd_runs(const hsap_attn_desc* desc, co
                                              float* dk_acc, float* dv_acc, void* hip_stream) {
   clear_error();
   return backward<false>(desc, q, k, v, d_o, nullptr, lse, delta, nullptr, nullptr, 0, doc_start, tiles_k, runs_k, num_runs_k,
-                         tiles_q, runs_q, num_runs_q, dq_acc, dk_acc, dv_acc, (hipStream_t)hip_stream);
+                         tiles_q, runs_q, num_runs_q, dq_acc, dk_acc, dv_acc, 0, (hipStream_t)hip_stream);
 }
 
 extern "C" hsap_status hsap_attn_bwd_bf16(const hsap_attn_desc* desc, const void* q, const void* k, const void* v,
@@ -1208,7 +1271,7 @@ extern "C" hsap_status hsap_attn_bwd_bf16(const hsap_attn_desc* desc, const void
                                           int64_t num_runs_q, void* dq, void* dk, void* dv, void* hip_stream) {
   clear_error();
   return backward<true>(desc, q, k, v, d_o, nullptr, lse, delta, nullptr, nullptr, 0, doc_start, tiles_k, runs_k, num_runs_k,
-                        tiles_q, runs_q, num_runs_q, dq, dk, dv, (hipStream_t)hip_stream);
+                        tiles_q, runs_q, num_runs_q, dq, dk, dv, 0, (hipStream_t)hip_stream);
 }
 
 namespace hsap {
@@ -1217,9 +1280,9 @@ hsap_status attn_bwd_bf16_delta(const hsap_attn_desc* desc, const void* q, const
                                 const int32_t* cu_seqlens, int32_t num_docs, int32_t* doc_start,
                                 const hsap_tile* tiles_k, const hsap_run* runs_k, int64_t num_runs_k,
                                 const hsap_tile* tiles_q, const hsap_run* runs_q, int64_t num_runs_q, void* dq,
-                                void* dk, void* dv, hipStream_t stream) {
+                                void* dk, void* dv, int key_blocks, hipStream_t stream) {
   if (!o || !cu_seqlens || num_docs < 1) HSAP_FAIL(HSAP_ERR_INVALID_ARG, "NULL o or no cumulative lengths");
   return backward<true>(desc, q, k, v, d_o, o, lse, nullptr, delta, cu_seqlens, num_docs, doc_start, tiles_k, runs_k,
-                        num_runs_k, tiles_q, runs_q, num_runs_q, dq, dk, dv, stream);
+                        num_runs_k, tiles_q, runs_q, num_runs_q, dq, dk, dv, key_blocks, stream);
 }
 }  // namespace hsap

@@ -75,6 +75,7 @@ struct hsap_executor {
   const hsap_run* d_runs_all = nullptr;
   const int32_t* d_merged_tiles = nullptr;
   const int32_t* d_zero_ktiles = nullptr;
+  int key_blocks = 0;             // of 32 per dK/dV workgroup, for the plan's k-major runs
   const int32_t* d_cu = nullptr;  // the plan's cu_seqlens (searched for document starts)
   int32_t num_docs = 0;
   std::vector<uint8_t> chunk_has_tiles;
@@ -304,6 +305,7 @@ hsap_status hsap_executor_plan(hsap_executor* ex, const int32_t* cu_seqlens, int
     if (st != HSAP_OK) return st;
   }
   ex->info.num_runs_k = RK;
+  if (RK) ex->key_blocks = plan_key_blocks(ex->desc, ex->geom, ex->runs_k.data(), RK, T);
   ex->info.num_runs_all = RA;
   // dK/dV rows of a chunk with tiles are written by the k-major run of their k-tile; the k-tiles
   // without one (no query of the shard reaches them) are zeroed by the backward instead
@@ -459,7 +461,7 @@ hsap_status hsap_executor_backward(hsap_executor* ex, const void* q, const void*
   if (st == HSAP_OK)
     st = attn_bwd_bf16_delta(&ex->desc, q, k, v, d_o, o, lse, ex->delta, ex->d_cu, ex->num_docs, ex->doc_start,
                              ex->d_tiles_k, ex->d_runs_k, ex->info.num_runs_k, ex->d_tiles_all, ex->d_runs_all,
-                             ex->info.num_runs_all, dq, dk, dv, stream);
+                             ex->info.num_runs_all, dq, dk, dv, ex->key_blocks, stream);
   return st;
 }
 

@@ -246,7 +246,11 @@ hsap_status attn_bwd_bf16_delta(const hsap_attn_desc* desc, const void* q, const
                                 const int32_t* cu_seqlens, int32_t num_docs, int32_t* doc_start,
                                 const hsap_tile* tiles_k, const hsap_run* runs_k, int64_t num_runs_k,
                                 const hsap_tile* tiles_q, const hsap_run* runs_q, int64_t num_runs_q, void* dq,
-                                void* dk, void* dv, hipStream_t stream);
+                                void* dk, void* dv, int key_blocks, hipStream_t stream);
+
+// Key blocks of 32 per dK/dV workgroup (attn_bwd_bf16_delta's key_blocks) for all k-major runs of a plan, longest
+// first (host), with num_tiles tiles in all.
+int plan_key_blocks(const hsap_attn_desc& d, const Geom& g, const hsap_run* runs, int64_t num_runs, int64_t num_tiles);
 hsap_status executor_forward(const hsap_attn_desc* desc, bool fused, const void* q, const void* k, const void* v,
                              const int32_t* cu_seqlens, int32_t num_docs, const hsap_tile* tiles,
                              const hsap_run* runs, int64_t num_runs, float* o_part, float* lse_part,

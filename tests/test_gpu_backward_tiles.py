@@ -125,6 +125,28 @@ def test_dk_keeps_p_in_32_bits(case):
         assert abs(along - 1.0) <= 2.0 ** -14, (case, along)
 
 
+# the executor's choice by the lengths of its plan's runs (the descriptor's choice in brackets)
+PLANS = [
+    (2048, 16, 16, 128, 128, 128, [300]),   # 128 keys (128), P in fp32 up to 1024 blocks
+    (2048, 15, 15, 128, 64, 128, [700]),    # 128 keys (128), 64-row q-tiles
+    (2048, 14, 14, 128, 128, 128, [2048]),  # 64 keys (128)
+    (2048, 36, 9, 128, 128, 128, [2048]),   # 32 keys (32), four query heads per K/V head
+    (2048, 22, 11, 128, 64, 64, [2048]),    # 64 keys (32)
+    (2048, 16, 16, 64, 64, 64, [2048]),     # 64 keys (64)
+]
+
+
+@pytest.mark.parametrize("case", PLANS)
+def test_backward_by_plan(case):
+    # the bars of test_backward_workgroup_shapes and test_dk_keeps_p_in_32_bits
+    c = _case(*case)
+    ref, got = c.run_oracle(), c.run_executor()
+    rep = compare_backward(got, ref)
+    assert max(rep.values()) <= 2.0 ** -7, (case, rep)
+    along = float(np.sum(got["dk"].astype(np.float64) * ref["dk"]) / np.sum(np.square(ref["dk"], dtype=np.float64)))
+    assert abs(along - 1.0) <= 2.0 ** -14, (case, along)
+
+
 @pytest.mark.parametrize("case", [CASES[1], CASES[5]])
 def test_backward_unaligned_outputs(case):
     # dK and dV 2 bytes (fp32 accumulators: 4 bytes) off a 16-byte boundary give the aligned bits
