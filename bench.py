@@ -445,18 +445,30 @@ def fwd_source_hash() -> str:
     return h.hexdigest()[:16]
 
 
+def key_streams(d: int, bm: int, items: int, keys: int) -> int:
+    """Key streams per workgroup of the forward and dQ kernels (key_streams() in hsap_internal.h)."""
+    if bm > 128 or keys < 1024:
+        return 1
+    if d == 64 and bm == 64:
+        return 4 if items <= 256 else 2 if items <= 512 else 1
+    return 2 if items <= (192 if d == 128 and bm == 128 else 256) else 1
+
+
 def fwd_kernel_name(res) -> str:
-    """The partial forward kernel the library dispatches for a workload's shapes (bf16 scores)."""
-    d, bm, bn = res["head_dim"], res["block_m"], res["block_n"]
-    return "attn_fwd_dl_kernel<%d, %d, %d, false, false, false, 1>" % (d, bn, bm // 32)
+    """The partial forward kernel the library dispatches for a workload's shapes (bf16 scores, up to 256 chunks)."""
+    d, bm, bn, p = res["head_dim"], res["block_m"], res["block_n"], res["sp_degree"]
+    items = res["batch"] * res["tokens"] // p // bm * res["heads_q"] * p
+    ks = key_streams(d, bm, items, res["tokens"] // p)
+    return "attn_fwd_dl_kernel<%d, %d, %d, false, false, false, %d>" % (d, bn, bm // 32, ks)
 
 
 def bwd_kernel_names(res) -> list:
-    """The two backward kernels the library dispatches for a workload's shapes (bf16 gradients; grids
-    of more than 1024 blocks of 32 keys, as every workload's here)."""
+    """The two backward kernels the executor dispatches for a workload (bf16 gradients); the keys per
+    dK/dV workgroup, and whether it holds P in fp32, follow the plan and are left open here."""
     d, bm, bn = res["head_dim"], res["block_m"], res["block_n"]
-    dkdv = "attn_bwd_dkdv_kernel<%d, %d, true, false>" % (d, 4 if d == 128 and bn == 128 else 2)
-    return [dkdv, "attn_bwd_dq_kernel<%d, %d, %d, true, false, 1>" % (d, bn, bm // 32)]
+    ks = key_streams(d, bm, res["batch"] * res["tokens"] // res["sp_degree"] // bm * res["heads_q"], res["tokens"])
+    return ["attn_bwd_dkdv_kernel<%d, *, true, false, *>" % d,
+            "attn_bwd_dq_kernel<%d, %d, %d, true, false, %d>" % (d, bn, bm // 32, ks)]
 
 
 def measured_traffic(workload: str):

@@ -101,12 +101,11 @@ constexpr int kMaxListQTiles = 2048;
 //
 // The two roles are two loops of their own.  Bound by the matrix cores and the LDS
 // reads of the operands, of which neither is saturated (latency of each wave's chain
-// LDS read -> MFMA -> exponentials).  Measured: head_dim 128, 4096 rows of one document
-// x 32 heads 305 -> 290 us (against one loop with a role test per product);
-// head_dim 64, 8192 rows x 32 heads over 8: 602 -> 429 us (against one wave per 32
-// keys doing all four products); tile-list call, 4096 rows x 12 heads over 4:
-// 498 -> 155 us (four streams of 32 keys).  (The last two with P handed over in fp16; in fp32, as now, the
-// whole training layer of the former shape takes 865 for 820 us, the ring pass of the latter 622 for 610.)
+// LDS read -> MFMA -> exponentials; MFMA busy 0.50 at head_dim 128, 0.30 at 64).  Measured, the
+// kernel alone: head_dim 128, 4096 rows of one document x 32 heads, 305 -> 290 us against
+// one loop with a role test per product; against one wave per 32 keys doing all four
+// products, P in fp32: head_dim 64, 8192 rows x 32 heads over 8, 602 -> 448 us; tile-list call,
+// 4096 rows x 12 heads over 4, 498 -> 156 us (four streams of 32 keys).
 //
 // LDS ring: three sub-tiles (t: products, t + 1: scores, t + 2: in flight) and
 // one barrier per iteration; KB = 1 at head_dim 128 has room for two only

@@ -8,8 +8,8 @@
 // wave w owns 32 query rows, so BM = 32 * WAVES.  Every listed k-tile of BN
 // keys is consumed in steps of KB = 64 keys.
 //
-// Per step the workgroup stages the step's K and V rows in LDS, both in their
-// natural [key][d] layout with 16-byte stores, and each wave computes the
+// Per step the workgroup holds the step's K and V rows in LDS, both in their
+// natural [key][d] layout, and each wave computes the
 // scores transposed, S^T = K Q^T, with Q held in registers as the MFMA B
 // operand.  In that orientation a lane holds one query (its column) and 16
 // keys per 32-key block, so the row max and row sum of the online softmax
@@ -19,9 +19,12 @@
 // per-lane key order matches the register order of the score block.
 //
 // Pipelining: the scores of step s + 1 are computed on the matrix cores while
-// the vector units run the softmax of step s.  K and V each have two LDS
-// slots; the next K/V rows load into registers during a step and are written
-// to the free slots at its end, one barrier per step.
+// the vector units run the softmax of step s.  Two kernels differ in how rows
+// reach LDS.  attn_fwd_dl_kernel moves them there directly (global_load_lds) and runs
+// every shape of up to 256 chunks but fp8 scores with 64-row q-tiles.
+// attn_fwd_kernel, for those and for more chunks, has two slots of padded rows for K and
+// for V; the next rows load into registers during a step and are written to the
+// free slots at its end, one barrier per step.
 // Scores are scaled by softmax_scale * log2(e) so the exponentials are exp2.
 // FULL tiles skip all mask arithmetic; MASKED tiles compare each key position
 // with the query's document start and position.  O is rescaled only when
@@ -68,6 +71,7 @@ struct FwdArgs {
 // score (-inf) must stay -inf: times 0 it would turn into NaN and poison the row.
 __device__ __forceinline__ float fp8_step_scale(float sl) { return fmaxf(sl, 1.17549435e-38f); }
 
+// The register-staged forward.
 // FP8: Q and K are e4m3 codes (scores S = (Q8 K8^T) * q_scale[h] * k_scale[chunk, g]
 // from the 32x32x64 fp8 MFMA, a K row held as 128 bytes), V and the rest as in bf16.
 template <int D, int BN, int WAVES, bool FUSED, bool FP8 = false, bool LIST = false>

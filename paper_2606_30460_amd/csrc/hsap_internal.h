@@ -149,11 +149,12 @@ __device__ inline void run_and_head(int bid, int hq, int hkv, int& run, int& h) 
 // is issued at kernel start and consumed after the prologue.  With per-position starts it is one
 // load.  From the cumulative lengths instead: a wave's 32 queries (lanes 0..31; lane l ^ 32 holds
 // the query of lane l) are 32 consecutive positions -- every piece of a shard is a multiple of
-// the 64-, 128- or 256-row q-tile -- so at most 31 document boundaries lie after the document of
-// lane 0's position g_lo, up to lane 31's position g_hi.  The wave loads 64 consecutive entries
+// the 64-, 128- or 256-row q-tile -- so at most 31 documents with tokens begin after lane 0's position
+// g_lo, up to lane 31's position g_hi.  The wave loads 64 consecutive entries
 // of cu_seqlens, starting at most 31 entries before the document of g_lo (a 64-way search in
 // rounds narrows the start when there are more than 32 entries), and each lane takes the largest
-// entry not above its position with ballots and lane reads: no further memory access.
+// entry not above its position with ballots and lane reads: no further memory access.  Repeated entries
+// (documents without tokens) can outnumber the window; then each lane searches the entries.
 struct DocWindow {
   int32_t w;           // cu[base + lane], or this lane's start when per-position starts are given
   int32_t g_lo, g_hi;  // positions of the wave's first and last query
@@ -185,7 +186,7 @@ __device__ __forceinline__ int32_t doc_window_start(const int32_t* cu, int32_t n
   const int32_t lo = __popcll(__builtin_amdgcn_ballot_w64(r.w <= r.g_lo)) - 1;    // document of g_lo
   const int32_t last = __popcll(__builtin_amdgcn_ballot_w64(r.w <= r.g_hi)) - 1;  // last boundary <= g_hi
   int32_t start = __builtin_amdgcn_readlane(r.w, lo);
-  if (last >= 63) {  // more boundaries than the window holds (not reachable with validated shapes)
+  if (last >= 63) {  // more entries than the window holds: documents without tokens among them
     int32_t l = 0, h = num_docs;
     while (h - l > 1) {
       const int32_t mid = (l + h) >> 1;
