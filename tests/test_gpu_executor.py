@@ -6,7 +6,8 @@ max|g - ref| / max|ref| <= 3e-2; the executor's gradients are bf16).  With the
 same q-major split the executor launches the same kernels over the same lists
 as the entry points called one by one, so O, LSE, the fused output and the
 gradients (each block written by its one owning run, as bf16 directly or as
-fp32 then converted) must be identical bit for bit.
+fp32 then converted) must be identical bit for bit.  (dK and dV: of the plans
+here, whose run lengths give the keys per workgroup that the descriptor gives.)
 """
 import sys
 
