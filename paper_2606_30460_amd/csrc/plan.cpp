@@ -56,6 +56,7 @@ class SplitCost {
   // The q-major runs of a planner's list: consecutive tiles of one (chunk, q-tile).
   bool add_runs(const hsap_tile* t, int64_t n) {
     tiles_ = n;
+    runs_.reserve((size_t)n);
     for (int64_t i = 0; i < n; ++i) {
       if (i == 0 || t[i].chunk != t[i - 1].chunk || t[i].q_tile != t[i - 1].q_tile) {
         if (t[i].chunk < 0 || t[i].chunk >= g_.P || t[i].q_tile < 0 || t[i].q_tile >= nq_) return false;
@@ -68,14 +69,17 @@ class SplitCost {
 
   // 0 (uncut) or the piece length of least time among a half, a third and a quarter of a chunk's k-tiles, none
   // below 4 tiles and the average load per resident workgroup.
-  int32_t best() const {
+  int32_t best() {
     const int64_t avg = (tiles_ * heads_ + resident_ - 1) / resident_;
     int32_t len = 0;
-    if (longest_ <= std::max<int64_t>(avg, 4)) return len;
+    if (std::max<int64_t>({avg, 4, (nk_ + 3) / 4}) >= longest_) return len;
+    scratch_.resize((size_t)(longest_ + 1 + nq_ + g_.P));
     double least = time(longest_);
+    int64_t before = longest_;
     for (int64_t pieces = 2; pieces <= 4; ++pieces) {
       const int64_t l = std::max<int64_t>({avg, 4, (nk_ + pieces - 1) / pieces});
-      if (l >= longest_) continue;
+      if (l >= before) continue;  // (the last candidate again, or no cut)
+      before = l;
       const double t = time((int32_t)l);
       if (t < least) {
         least = t;
@@ -94,30 +98,38 @@ class SplitCost {
     double wave_step, wave;   // us of a SIMD's work: a wave's step, a wave's start and end
   };
 
-  double time(int32_t len) const {
-    std::vector<int32_t> lengths((size_t)longest_ + 1, 0);   // pieces of each length
-    std::vector<int32_t> pieces((size_t)nq_, 0);             // of each q-tile
-    std::vector<int32_t> slots((size_t)g_.P, 0);             // a chunk's slots: the most pieces a run of it has
+  double time(int32_t len) {
+    std::fill(scratch_.begin(), scratch_.end(), 0);
+    int32_t* const lengths = scratch_.data();      // pieces of each length
+    int32_t* const pieces = lengths + longest_ + 1;  // of each q-tile
+    int32_t* const slots = pieces + nq_;           // a chunk's slots: the most pieces a run of it has
     for (const Run& r : runs_) {
-      const int32_t p = (r.count + len - 1) / len, a = r.count / p, longer = r.count % p;
-      lengths[(size_t)a] += p - longer;
-      if (longer) lengths[(size_t)a + 1] += longer;
-      pieces[(size_t)r.q_tile] += p;
-      slots[(size_t)r.chunk] = std::max(slots[(size_t)r.chunk], p);
+      int32_t p = 1, a = r.count;
+      if (a > len) {
+        p = (r.count + len - 1) / len;
+        a = r.count / p;
+        const int32_t longer = r.count - a * p;
+        lengths[a] += p - longer;
+        lengths[a + 1] += longer;
+      } else {
+        ++lengths[a];
+      }
+      pieces[r.q_tile] += p;
+      slots[r.chunk] = std::max(slots[r.chunk], p);
     }
     int64_t merged = 0, busy = 0, parts = 0;
-    for (const int32_t p : pieces) {
-      merged += p > 1;
-      busy += p > 1 ? p : 0;
+    for (int64_t t = 0; t < nq_; ++t) {
+      merged += pieces[t] > 1;
+      busy += pieces[t] > 1 ? pieces[t] : 0;
     }
-    for (const int32_t p : slots) parts += p;
+    for (int32_t c = 0; c < g_.P; ++c) parts += slots[c];
     if (len < longest_ && parts > HSAP_MAX_MERGE_PARTS) return HUGE_VAL;  // more than one merge takes
     // the longest piece, and the lengths around the last resident workgroup, longest first
     int64_t seen = 0, first = 0, last = 0, next = 0;
     for (int64_t l = longest_; l > 0 && !next; --l) {
-      if (!lengths[(size_t)l]) continue;
+      if (!lengths[l]) continue;
       if (!first) first = l;
-      const int64_t until = seen + (int64_t)lengths[(size_t)l] * heads_;
+      const int64_t until = seen + lengths[l] * heads_;
       if (seen < resident_ && until >= resident_) last = l;
       if (until > resident_) next = l;
       seen = until;
@@ -136,6 +148,7 @@ class SplitCost {
   double row_bytes_;
   Constants c_;
   std::vector<Run> runs_;
+  std::vector<int32_t> scratch_;
 };
 
 static thread_local std::string g_last_error;
